@@ -97,6 +97,12 @@ def slab_points(prob):
     return (int(m1.max()) - int(m1.min()) + 1) * n2 * n3
 
 
+def columns(prob):
+    """Per k-point, the z columns (m1, m2) that hold sphere points."""
+    off = prob.pw_offsets
+    return [len(np.unique(prob.miller[off[k]:off[k + 1], :2], axis=0)) for k in range(len(prob.npw))]
+
+
 def kernel_model(name, prob, nb, launches):
     """Algorithmic (bytes, flops counted, flops executed) of ONE launch of a library kernel.
 
@@ -107,6 +113,10 @@ def kernel_model(name, prob, nb, launches):
       yz_inv : nb cb sum_k (npw_k + S)          read psi, write the slab planes
       xpass  : nb cb 2 S nk + launches 8 N      slab in and out, V once per launch
       yz_fwd : nb cb sum_k (S + 2 npw_k)        slab in, psi in (kinetic), H psi out
+    and, with L_k = ncol_k N3 (the z columns that hold sphere points):
+      z_inv  : nb cb sum_k (npw_k + L_k) + 16 N read psi, write the columns; V transposed
+      plane  : nb cb 2 sum_k L_k + launches 8 N columns in and out, V once per launch
+      z_fwd  : nb cb sum_k (L_k + 2 npw_k)      columns in, psi in (kinetic), H psi out
       gemm_cn: flops 8 nproj nb sum_k npw_k     counted complex flops; the kernel's 3M
                                                 products execute 6 nproj nb sum npw_k
       gemm_nn: flops 8 nb sum_k npw_k nproj     likewise (6 executed)
@@ -119,7 +129,11 @@ def kernel_model(name, prob, nb, launches):
     S = slab_points(prob)
     npj = prob.nproj
     tot = sum(npw)
+    L = [c * n3 for c in columns(prob)]
     per_step = {
+        "z_inv": (nb * cb * sum(n + c for n, c in zip(npw, L)) + 16 * N, 0, 0),
+        "plane": (nb * cb * 2 * sum(L) + launches * 8 * N, 0, 0),
+        "z_fwd": (nb * cb * sum(c + 2 * n for n, c in zip(npw, L)), 0, 0),
         "yz_inv": (nb * cb * sum(n + S for n in npw), 0, 0),
         "xpass": (nb * cb * 2 * S * nk + launches * 8 * N, 0, 0),
         "yz_fwd": (nb * cb * sum(S + 2 * n for n in npw), 0, 0),
@@ -144,6 +158,9 @@ KERNEL_SOURCES = {
     "yz_inv": ["paper_2501_08697_amd/csrc/local.hip", "paper_2501_08697_amd/csrc/fft_device.hpp"],
     "xpass": ["paper_2501_08697_amd/csrc/local.hip", "paper_2501_08697_amd/csrc/fft_device.hpp"],
     "yz_fwd": ["paper_2501_08697_amd/csrc/local.hip", "paper_2501_08697_amd/csrc/fft_device.hpp"],
+    "z_inv": ["paper_2501_08697_amd/csrc/columns.hpp", "paper_2501_08697_amd/csrc/fft_device.hpp"],
+    "plane": ["paper_2501_08697_amd/csrc/columns.hpp", "paper_2501_08697_amd/csrc/fft_device.hpp"],
+    "z_fwd": ["paper_2501_08697_amd/csrc/columns.hpp", "paper_2501_08697_amd/csrc/fft_device.hpp"],
     "gemm_cn": ["paper_2501_08697_amd/csrc/gemm.hip"],
     "gemm_nn": ["paper_2501_08697_amd/csrc/gemm.hip"],
 }
@@ -152,23 +169,22 @@ KERNEL_SOURCES = {
 def local_model_bytes(prob):
     """Per band, averaged over the k-points: the pruned 5-pass model's bytes for the
     local term (z on the disk of columns that hold sphere points, y on the slab, x on
-    all; cb N 4 (f_disk + f_slab) + 2 cb npw) and the bytes the three fused plane
-    passes here move (4 cb S + 3 cb npw, the disk staying in LDS)."""
+    all; cb N 4 (f_disk + f_slab) + 2 cb npw) and the bytes the three column passes
+    here move (4 cb ncol N3 + 3 cb npw, the slab staying in LDS)."""
     cb = 16
     n1, n2, n3 = prob.fft
     N = n1 * n2 * n3
     off = prob.pw_offsets
     model = ours = fd = fs = 0.0
     nk = len(prob.npw)
-    for k in range(nk):
+    for k, cols in enumerate(columns(prob)):
         m = prob.miller[off[k]:off[k + 1]]
         npw = int(prob.npw[k])
-        cols = len({(int(a) % n1, int(b) % n2) for a, b in zip(m[:, 0], m[:, 1])})
         f_disk = cols / (n1 * n2)
         nslab_k = int(m[:, 0].max()) - int(m[:, 0].min()) + 1
         f_slab = nslab_k / n1
         model += cb * N * 4 * (f_disk + f_slab) + 2 * cb * npw
-        ours += 4 * cb * slab_points(prob) + 3 * cb * npw
+        ours += 4 * cb * cols * n3 + 3 * cb * npw
         fd += f_disk
         fs += f_slab
     return model / nk, ours / nk, fd / nk, fs / nk
@@ -360,7 +376,7 @@ def roofline_of(rows, prob, nb, workload, mp):
 
 
 def local_term_of(rows, prob, nb, mp):
-    t_local = sum(rows[k]["avg_ms"] * rows[k]["launches_per_step"] for k in ("yz_inv", "xpass", "yz_fwd") if k in rows)
+    t_local = sum(rows[k]["avg_ms"] * rows[k]["launches_per_step"] for k in ("z_inv", "plane", "z_fwd", "yz_inv", "xpass", "yz_fwd") if k in rows)
     model_b, ours_b, f_disk, f_slab = local_model_bytes(prob)
     nbt = nb * prob.nk
     lt = {"ms_per_step": t_local, "f_disk": f_disk, "f_slab": f_slab,

@@ -403,13 +403,16 @@ int abacus_pw_profile_read(char *buf, int size);
 
 /*
  * Tuning knobs, process-wide (the autotuner sets these; 0 = library default).
- * band_batch   bands per local-term batch (slab work space = band_batch planes sets)
+ * band_batch   bands per local-term batch (work space = band_batch bands of planes or columns; 0: 64
+ *              bands of planes, 4 GiB of columns)
  * splitk_chunk K chunk of the split-K projection GEMM (multiple of 16)
- * yz_bands     bands handled by one y-z plane work-group
- * x_bands      bands handled by one x-pass work-group
- * yz_mode      y-z plane kernels: 0 automatic (whole plane in LDS when it fits), 1 whole
- *              plane, 2 compact (only the plane's z-column rows in LDS, y transforms in
- *              j3 chunks); planes that do not fit whole always use the compact form
+ * yz_bands     bands handled by one y-z plane (or z column) work-group
+ * x_bands      bands handled by one x-pass (or x-y plane) work-group
+ * yz_mode      plane kernels: 0 automatic (FP64 H psi: z columns between the passes and the x and
+ *              y transforms of a plane in one, where the plane fits in LDS; else y-z planes, whole
+ *              in LDS when they fit), 1 whole y-z planes, 2 compact y-z planes (only the plane's
+ *              z-column rows in LDS, y transforms in j3 chunks); planes that do not fit whole
+ *              always use the compact form
  * overlap      0 default (2), 1 the projector GEMMs run on a second stream of the library
  *              (default priority) beside the local term: the projections from the start,
  *              each band batch's B Q as soon as its local term is done; events order the

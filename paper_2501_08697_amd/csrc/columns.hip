@@ -1,0 +1,96 @@
+// Launchers of the column passes (columns.hpp).
+#include <algorithm>
+
+#include "columns.hpp"
+
+namespace apw {
+
+// The x transform runs one task per thread and phase (C max(A1, B1) <= threads), the y
+// transform's tasks wrap around. C is the widest divisor of N2 that the threads and LDS allow:
+// at 120^3 30 columns took 44.9 ms of plane passes per call of 4,096 bands, 24 took 48.1 and
+// 20 took 55 (shorter chunks leave threads without a task in F).
+PlaneShape plane_shape(const Plan &P) {
+    PlaneShape s{0, 0, P.N2 | 1, 0};
+    int a1, b1, a2, b2;
+    if (!lds_split_host(P.N1, &a1, &b1) || !lds_split_host(P.N2, &a2, &b2)) return s;
+    if (P.N1 != P.N2 && !(P.zero_band[0] && P.zero_band[1])) return s;
+    const int m1 = std::max(a1, b1), m2 = std::max(a2, b2), nt = plane_threads(P.N1, P.N2);
+    auto lds = [&](int C) {
+        return ((size_t)P.nslab * s.ldr + (size_t)(P.N1 - P.nslab) * C + P.N1 + P.N2 + 1) * sizeof(z64);
+    };
+    for (int C = std::min(P.N2, nt / m1); C >= 1; --C)
+        if (P.N2 % C == 0 && lds(C) <= 160 * 1024) {
+            s.C = C;
+            break;
+        }
+    if (s.C == 0) return s;
+    s.lds = lds(s.C);
+    s.NT = std::min(nt, (std::max(s.C * m1, P.nslab * m2) + 63) / 64 * 64);
+    return s;
+}
+
+// Bands per z-pass work-group: up to 4 share the tables read once, while the launch keeps
+// 2048 work-groups (eight a CU).
+static int z_bands(const ColumnsCall &c, int ngrp) {
+    if (g_yz_bands > 0) return std::min(g_yz_bands, c.ba.bbt);
+    int bpw = 4;
+    while (bpw > 1 && ngrp * c.nkb * ceil_div(c.ba.bbt, bpw) < 2048) bpw /= 2;
+    return std::min(bpw, c.ba.bbt);
+}
+
+template <int N> static int launch_z_inv(const ColumnsCall &c, const void *psi, const double *v) {
+    const Plan &P = *c.P;
+    const int ngrp = ceil_div(P.max_ncol, ZTile<N>::C), bpw = z_bands(c, ngrp);
+    const int nblk = ngrp * c.nkb * ceil_div(c.ba.bbt, bpw);
+    const int nvt = v ? P.N1 * ceil_div(P.N2, kVtTile) * ceil_div(P.N3, kVtTile) : 0;
+    auto kernel = P.zero_band[2] ? k_z_inv<N, double, double, true> : k_z_inv<N, double, double, false>;
+    KernelTimer kt("z_inv", c.st);
+    hipLaunchKernelGGL(kernel, dim3(nblk + nvt), dim3(ZTile<N>::NT), 0, c.st, static_cast<const z64 *>(psi),
+                       P.kdesc + c.k0, c.ba, static_cast<const z64 *>(P.tw64[2]), static_cast<z64 *>(c.col), P.ldc,
+                       ngrp, bpw, nblk, v, static_cast<double *>(c.vt), P.N1, P.N2);
+    return check_launch("z_inv");
+}
+
+template <int N> static int launch_z_fwd(const ColumnsCall &c, const void *psi, void *hpsi) {
+    const Plan &P = *c.P;
+    const int ngrp = ceil_div(P.max_ncol, ZTile<N>::C), bpw = z_bands(c, ngrp);
+    auto kernel = P.zero_band[2] ? k_z_fwd<N, double, double, true> : k_z_fwd<N, double, double, false>;
+    KernelTimer kt("z_fwd", c.st);
+    hipLaunchKernelGGL(kernel, dim3(ngrp * c.nkb * ceil_div(c.ba.bbt, bpw)), dim3(ZTile<N>::NT), 0, c.st,
+                       static_cast<const z64 *>(c.col), P.ldc, P.kdesc + c.k0, c.ba,
+                       static_cast<const z64 *>(P.tw64[2]), static_cast<const z64 *>(psi), static_cast<z64 *>(hpsi),
+                       1.0 / (double)P.N, ngrp, bpw);
+    return check_launch("z_fwd");
+}
+
+int columns_inverse(const ColumnsCall &c, const void *psi, const double *v) {
+    switch (c.P->N3) {
+#define APW_CASE(n) case n: return launch_z_inv<n>(c, psi, v);
+        APW_LENGTHS(APW_CASE)
+#undef APW_CASE
+        default:
+            return set_error(ABACUS_PW_EBAD_FFT_SIZE, "unsupported grid length");
+    }
+}
+
+int columns_forward(const ColumnsCall &c, const void *psi, void *hpsi) {
+    switch (c.P->N3) {
+#define APW_CASE(n) case n: return launch_z_fwd<n>(c, psi, hpsi);
+        APW_LENGTHS(APW_CASE)
+#undef APW_CASE
+        default:
+            return set_error(ABACUS_PW_EBAD_FFT_SIZE, "unsupported grid length");
+    }
+}
+
+int columns_plane(const ColumnsCall &c) {
+    switch (c.P->N1) {
+#define APW_CASE(n) case n: return columns_plane_n1<n>(c);
+        APW_LENGTHS(APW_CASE)
+#undef APW_CASE
+        default:
+            return set_error(ABACUS_PW_EBAD_FFT_SIZE, "unsupported grid length");
+    }
+}
+
+}  // namespace apw

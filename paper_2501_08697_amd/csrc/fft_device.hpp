@@ -68,11 +68,26 @@ APW_LDS_SPLIT(120, 15, 8)
 APW_LDS_SPLIT(128, 16, 8)
 #undef APW_LDS_SPLIT
 
+// Grid lengths with a compiled transform.
+#define APW_LENGTHS(X) \
+    X(8) X(12) X(16) X(18) X(20) X(24) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(54) X(60) X(64) X(72) X(80) \
+    X(81) X(90) X(96) X(100) X(108) X(120) X(128)
+
 // ------------------------------------------------------------ codelets ----
 // w = exp(S 2 pi i e / N) from the literal tables; e == 0 is skipped by the
 // caller so multiplications by one vanish after unrolling.
 template <int N, int S, typename T> __device__ __forceinline__ cx<T> codelet_tw(int e) {
     return cx<T>{static_cast<T>(CodeletTw<N>::c[e]), static_cast<T>(S * CodeletTw<N>::s[e])};
+}
+
+// a times codelet_tw<N, S>(e). Quarter turns are exact swaps (the table's entries there are
+// 0 and 1, so the products would only add zeros).
+template <int N, int S, typename T> __device__ __forceinline__ cx<T> mul_tw(cx<T> a, int e) {
+    if (e == 0) return a;
+    if (4 * e == N) return mul_si<S>(a);
+    if (2 * e == N) return cx<T>{-a.re, -a.im};
+    if (4 * e == 3 * N) return mul_si<-S>(a);
+    return cmul(a, codelet_tw<N, S, T>(e));
 }
 
 template <int N, int S, typename T> struct RegDft {
@@ -87,8 +102,7 @@ template <int N, int S, typename T> struct RegDft {
             RegDft<A, S, T>::run(a);
 #pragma unroll
             for (int ka = 0; ka < A; ++ka) {
-                const int e = (jb * ka) % N;
-                t[ka * B + jb] = (e == 0) ? a[ka] : cmul(a[ka], codelet_tw<N, S, T>(e));
+                t[ka * B + jb] = mul_tw<N, S, T>(a[ka], (jb * ka) % N);
             }
         }
 #pragma unroll
@@ -154,6 +168,87 @@ template <int S, typename T> struct RegDft<5, S, T> {
         v[4] = a1 - b1;
         v[2] = a2 + b2;
         v[3] = a2 - b2;
+    }
+};
+
+// Inputs of a length-N codelet that are zero when the transform's frequencies are at most a
+// quarter of its length (the usual grid: twice the sphere's diameter): with k = ka + A kb the
+// slots kb in [ZeroBand<N>::lo, hi) of every ka.
+template <int N> struct ZeroBand {
+    static constexpr int lo = N / 4 + 1, hi = N - (N + 3) / 4;
+    static constexpr bool zero(int q) { return q >= lo && q < hi; }
+};
+
+// RegDft<N, +1> of inputs that are zero in ZeroBand<N> (those are not read). The same sums
+// without the zero terms, so the same values.
+template <int N, typename T> struct RegDftZ {
+    static constexpr int A = Split<N>::A, B = Split<N>::B;
+    __device__ __forceinline__ static void run(cx<T> *v) {
+        using Z = ZeroBand<N>;
+        cx<T> t[N];
+#pragma unroll
+        for (int jb = 0; jb < B; ++jb) {
+            cx<T> a[A];
+            if constexpr (A == 2) {
+                if (Z::zero(jb + B)) {
+                    a[0] = a[1] = v[jb];
+                } else if (Z::zero(jb)) {
+                    a[0] = v[jb + B];
+                    a[1] = cx<T>{-v[jb + B].re, -v[jb + B].im};
+                } else {
+                    a[0] = v[jb] + v[jb + B];
+                    a[1] = v[jb] - v[jb + B];
+                }
+            } else {
+                static_assert(A == 3, "codelet");
+                const T h = static_cast<T>(0.8660254037844386);
+                cx<T> x = v[jb], t1, t2;
+                if (Z::zero(jb + B) && Z::zero(jb + 2 * B)) {
+                    a[0] = a[1] = a[2] = x;
+                } else {
+                    if (Z::zero(jb + B)) {
+                        t1 = v[jb + 2 * B];
+                        t2 = cx<T>{-t1.re, -t1.im};
+                    } else if (Z::zero(jb + 2 * B)) {
+                        t1 = t2 = v[jb + B];
+                    } else {
+                        t1 = v[jb + B] + v[jb + 2 * B];
+                        t2 = v[jb + B] - v[jb + 2 * B];
+                    }
+                    cx<T> m = x - t1 * static_cast<T>(0.5);
+                    cx<T> r = mul_si<+1>(t2 * h);
+                    a[0] = x + t1;
+                    a[1] = m + r;
+                    a[2] = m - r;
+                }
+            }
+#pragma unroll
+            for (int ka = 0; ka < A; ++ka) t[ka * B + jb] = mul_tw<N, +1, T>(a[ka], (jb * ka) % N);
+        }
+#pragma unroll
+        for (int ka = 0; ka < A; ++ka) {
+            cx<T> z[B];
+#pragma unroll
+            for (int jb = 0; jb < B; ++jb) z[jb] = t[ka * B + jb];
+            RegDft<B, +1, T>::run(z);
+#pragma unroll
+            for (int kb = 0; kb < B; ++kb) v[ka + A * kb] = z[kb];
+        }
+    }
+};
+template <typename T> struct RegDftZ<4, T> {   // v[2] = 0
+    __device__ __forceinline__ static void run(cx<T> *v) {
+        cx<T> a = v[0], c = v[1] + v[3], d = mul_si<+1>(v[1] - v[3]);
+        v[0] = a + c;
+        v[2] = a - c;
+        v[1] = a + d;
+        v[3] = a - d;
+    }
+};
+template <typename T> struct RegDftZ<5, T> {   // v[2] = 0
+    __device__ __forceinline__ static void run(cx<T> *v) {
+        v[2] = cx<T>{T(0), T(0)};
+        RegDft<5, +1, T>::run(v);
     }
 };
 

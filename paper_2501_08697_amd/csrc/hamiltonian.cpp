@@ -124,7 +124,7 @@ void hwork_sizes(const Plan &P, int prec, int nb, int k0, int k1, size_t sz[kHWo
     const int fft_prec = prec == ABACUS_PW_FP64 ? 0 : 1;
     const int gemm_prec = prec == ABACUS_PW_FP64 ? 0 : 1;
     for (int i = 0; i < kHWorkParts; ++i) sz[i] = 0;
-    sz[0] = local_slab_bytes(P, fft_prec, (k1 - k0) * default_band_batch(P, nb));
+    sz[0] = local_work_bytes(P, fft_prec, k1 - k0, nb);
     if (P.nproj == 0) return;
     const size_t gb = gemm_prec == 0 ? 16 : 8;
     sz[1] = (size_t)nb * P.nproj * gb * (k1 - k0);
@@ -152,7 +152,6 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
     const int gemm_prec = prec == ABACUS_PW_FP64 ? 0 : 1;
     const size_t ib = io_prec == 0 ? 16 : 8;     // bytes per psi element
     APW_TRY(local_supported(P, fft_prec));
-    const int bb = default_band_batch(P, nb);
     // work buffers: the plan's (grown as needed) or carved from the caller's work space
     size_t sz[kHWorkParts];
     hwork_sizes(P, prec, nb, k0, k1, sz);
@@ -176,7 +175,7 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
     void *slab = w[0], *projq = w[1], *gemm_part = w[2], *psibf = w[3], *qbf = w[4], *tmp_io = w[5];
     if (refresh_copies) APW_TRY(operator_copies(p, P, fft_prec == 1, gemm_prec == 1 && !bf, st, bf));
     const void *v = fft_prec == 0 ? static_cast<const void *>(p.vloc) : P.vloc32.ptr;
-    if (P.nproj == 0) return local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, bb, st);
+    if (P.nproj == 0) return local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, st);
 
     const size_t gb = gemm_prec == 0 ? 16 : 8;   // bytes per element of Q (complex64 in the BF16 mode)
     const size_t qk = (size_t)nb * P.nproj * gb; // Q bytes per k-point
@@ -237,10 +236,10 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
         return ABACUS_PW_OK;
     };
     if (!overlap) {
-        APW_TRY(local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, bb, st));
+        APW_TRY(local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, st));
         return add_bq(0, nb, st);
     }
-    APW_TRY(local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, bb, st, [&](int b0, int bbt) -> int {
+    APW_TRY(local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, st, [&](int b0, int bbt) -> int {
         APW_TRY(order(ss->step, st, gs));
         return add_bq(b0, bbt, gs);
     }));

@@ -1,5 +1,7 @@
 // Local-potential term of H psi on the real-space grid (plane-wave KS equation,
-// Sec. III.A; V_local of the pseudopotential split, Sec. II.A):
+// Sec. III.A; V_local of the pseudopotential split, Sec. II.A). FP64 runs the column passes of
+// columns.hpp wherever a plane fits them; this file holds the passes over whole grid planes that
+// FP32 and the mixed modes, the density and the adjoint use, and FP64 where it does not:
 //
 //   (V psi)(G) = (1/N) sum_j e^{-iG.r_j} V(r_j) sum_{G'} psi(G') e^{+iG'.r_j}
 //
@@ -16,24 +18,14 @@
 //           rows, gather the sphere points, write |k+G|^2 psi + (1/N) (V psi).
 // HBM traffic per band: psi and H psi once, four passes over the slab
 // (nslab * N2 * N3 complex), V once per band tile.
+#include "columns.hpp"
 #include "fft_device.hpp"
 #include "local.hpp"
 #include "plan.hpp"
 
+#include <algorithm>
+
 namespace apw {
-
-template <typename T> __device__ __forceinline__ cx<T> czero() { return cx<T>{T(0), T(0)}; }
-
-int lds_split_host(int n, int *a, int *b);
-
-// A band batch spread over the k-points [k0, k0 + nk) of a call: at every k the
-// bands [b0, b0 + bbt) of that k's [nb_total][npw_k] block; off0 = pw_off[k0].
-struct BatchArgs {
-    int64_t nb_total;
-    int64_t off0;
-    int b0;
-    int bbt;
-};
 
 // Block y index -> (k-point, band range inside the batch) for work-groups of bpw bands.
 // The planes of one band group are logically consecutive (x = plane), so the
@@ -1076,10 +1068,6 @@ static int launch_x(const Plan &P, const void *vloc, void *slab, int nbands, hip
     return check_launch("xpass");
 }
 
-#define APW_LENGTHS(X) \
-    X(8) X(12) X(16) X(18) X(20) X(24) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(54) X(60) X(64) X(72) X(80) \
-    X(81) X(90) X(96) X(100) X(108) X(120) X(128)
-
 int local_length_supported(int n) {
     switch (n) {
 #define APW_CASE(n) case n:
@@ -1211,26 +1199,64 @@ int local_sum_parts(const Plan &P, const double *part, int G, double scale, doub
     return check_launch("gradv_reduce");
 }
 
+// Whether the call's planes run through the column passes (columns.hpp): FP64 in the automatic
+// plane mode, a plane that fits in LDS, and a kernel for the pair of lengths. They took the
+// FP64 local term at 72^3 (128 bands) from 461 to 345 us, at 120^3 (4,096 bands) from 78.9 to
+// 58.6 ms. In FP32 the plane pass is bound by VALU instructions, which are as many as in FP64
+// (144 of 245 us at 72^3): 216 against 243 us there, but 16.2 against 13.9 ms at 128^3, so FP32
+// keeps the slab passes.
+static bool use_columns(const Plan &P, int fft_prec) {
+    return fft_prec == 0 && g_yz_mode == 0 && plane_shape(P).C > 0;
+}
+
+static size_t column_bytes(const Plan &P, int fft_prec) {
+    return (size_t)P.N3 * P.ldc * (fft_prec == 0 ? 16 : 8);
+}
+
+int local_band_batch(const Plan &P, int fft_prec, int nkb, int nb) {
+    if (g_band_batch > 0) return std::min(g_band_batch, nb);
+    if (!use_columns(P, fft_prec)) return std::min(64, nb);
+    // as many bands as 4 GiB of columns hold: at 120^3 x 8 k-points the plane passes of a call took
+    // 39.5 ms with 4 GiB, 41.9 with 1 GiB and 42.5 with 192 MiB (batches that stay in the 256 MB
+    // infinity cache gain nothing back; every launch's last round of work-groups costs)
+    const size_t per = column_bytes(P, fft_prec) * nkb;
+    return (int)std::max<size_t>(1, std::min<size_t>(nb, (size_t(4) << 30) / per));
+}
+
+size_t local_work_bytes(const Plan &P, int fft_prec, int nkb, int nb) {
+    const int nvb = nkb * local_band_batch(P, fft_prec, nkb, nb);
+    if (!use_columns(P, fft_prec)) return local_slab_bytes(P, fft_prec, nvb);
+    return (column_bytes(P, fft_prec) * nvb + 255) / 256 * 256 + (size_t)P.N * (fft_prec == 0 ? 8 : 4);
+}
+
+template <typename T, typename TIO>
+static int slab_batch(const Plan &P, int k0, int nkb, const BatchArgs &ba, const void *vloc, const void *psi,
+                      void *hpsi, void *slab, hipStream_t st) {
+    APW_TRY((dispatch_yz<T, TIO>(true, P, k0, nkb, ba, psi, nullptr, slab, st)));
+    APW_TRY((dispatch_x<T>(P, vloc, slab, nkb * ba.bbt, st)));
+    return dispatch_yz<T, TIO>(false, P, k0, nkb, ba, psi, hpsi, slab, st);
+}
+
 int local_term(const Plan &P, int k0, int k1, int fft_prec, int io_prec, const void *vloc, const void *psi,
-               void *hpsi, int nb, void *slab, int band_batch, hipStream_t st,
-               const std::function<int(int, int)> &after_batch) {
+               void *hpsi, int nb, void *slab, hipStream_t st, const std::function<int(int, int)> &after_batch) {
     const int nkb = k1 - k0;
+    const int band_batch = local_band_batch(P, fft_prec, nkb, nb);
+    const bool cols = use_columns(P, fft_prec);
+    char *vt = static_cast<char *>(slab) + (column_bytes(P, fft_prec) * nkb * band_batch + 255) / 256 * 256;
+    const double *v64 = static_cast<const double *>(vloc);
     for (int b0 = 0; b0 < nb; b0 += band_batch) {
         const BatchArgs ba{nb, P.pw_off[k0], b0, std::min(band_batch, nb - b0)};
-        const int nv = nkb * ba.bbt;   // (k, band) planes sets in this batch
-        if (fft_prec == 0) {
-            APW_TRY((dispatch_yz<double, double>(true, P, k0, nkb, ba, psi, nullptr, slab, st)));
-            APW_TRY((dispatch_x<double>(P, vloc, slab, nv, st)));
-            APW_TRY((dispatch_yz<double, double>(false, P, k0, nkb, ba, psi, hpsi, slab, st)));
-        } else if (io_prec == 1) {
-            APW_TRY((dispatch_yz<float, float>(true, P, k0, nkb, ba, psi, nullptr, slab, st)));
-            APW_TRY((dispatch_x<float>(P, vloc, slab, nv, st)));
-            APW_TRY((dispatch_yz<float, float>(false, P, k0, nkb, ba, psi, hpsi, slab, st)));
-        } else {
-            APW_TRY((dispatch_yz<float, double>(true, P, k0, nkb, ba, psi, nullptr, slab, st)));
-            APW_TRY((dispatch_x<float>(P, vloc, slab, nv, st)));
-            APW_TRY((dispatch_yz<float, double>(false, P, k0, nkb, ba, psi, hpsi, slab, st)));
-        }
+        const ColumnsCall c{&P, k0, nkb, ba, slab, vt, st};
+        if (cols) {
+            APW_TRY(columns_inverse(c, psi, b0 == 0 ? v64 : nullptr));
+            APW_TRY(columns_plane(c));
+            APW_TRY(columns_forward(c, psi, hpsi));
+        } else if (fft_prec == 0)
+            APW_TRY((slab_batch<double, double>(P, k0, nkb, ba, vloc, psi, hpsi, slab, st)));
+        else if (io_prec == 1)
+            APW_TRY((slab_batch<float, float>(P, k0, nkb, ba, vloc, psi, hpsi, slab, st)));
+        else
+            APW_TRY((slab_batch<float, double>(P, k0, nkb, ba, vloc, psi, hpsi, slab, st)));
         if (after_batch) APW_TRY(after_batch(b0, ba.bbt));
     }
     return ABACUS_PW_OK;

@@ -15,8 +15,6 @@
 
 namespace apw {
 
-int lds_split_host(int n, int *a, int *b);   // local_tables.cpp
-
 int g_band_batch = 0;
 int g_splitk_chunk = 0;
 int g_yz_bands = 0;
@@ -222,8 +220,9 @@ int build_plan(const abacus_pw_problem *p, Plan &P, hipStream_t st) {
     // per-k plane tables
     std::vector<unsigned char> img;
     struct Offs {
-        size_t pt_off, pt_g, pt_pos, row_off, row_list, kin, kin32;
+        size_t pt_off, pt_g, pt_pos, row_off, row_list, kin, kin32, zslot, ymap, cpos;
     };
+    std::vector<std::vector<int>> rows_off(p->nk), rows_list(p->nk);
     std::vector<Offs> koffs(p->nk);
     for (int k = 0; k < p->nk; ++k) {
         const int *mk = p->miller + 3 * P.pw_off[k];
@@ -261,6 +260,9 @@ int build_plan(const abacus_pw_problem *p, Plan &P, hipStream_t st) {
             kin[g] = q[0] * q[0] + q[1] * q[1] + q[2] * q[2];
             kin32[g] = (float)kin[g];
         }
+        P.max_ncol = std::max(P.max_ncol, (int)row_list.size());
+        rows_off[k] = row_off;
+        rows_list[k] = row_list;
         koffs[k].pt_off = put(img, pt_off);
         koffs[k].pt_g = put(img, pt_g);
         koffs[k].pt_pos = put(img, pt_pos);
@@ -269,10 +271,44 @@ int build_plan(const abacus_pw_problem *p, Plan &P, hipStream_t st) {
         koffs[k].kin = put(img, kin);
         koffs[k].kin32 = put(img, kin32);
     }
+    // z columns of every k-point: sphere index by (z slot, column), column by (y slot, slab row)
+    P.ldc = (P.max_ncol + 15) / 16 * 16;
+    for (int k = 0; k < p->nk; ++k) {
+        const int *mk = p->miller + 3 * P.pw_off[k];
+        std::vector<int> zslot((size_t)P.N3 * P.ldc, -1);
+        std::vector<unsigned short> ymap((size_t)P.N2 * P.nslab, 0xffff), cpos(P.ldc, 0);
+        for (int s = 0; s < P.nslab; ++s)
+            for (int q = rows_off[k][s]; q < rows_off[k][s + 1]; ++q) {
+                ymap[(size_t)rows_list[k][q] * P.nslab + s] = (unsigned short)q;
+                cpos[q] = (unsigned short)(s * (P.N2 | 1) + rows_list[k][q]);
+            }
+        for (int g = 0; g < p->npw[k]; ++g) {
+            const int *m = mk + 3 * g;
+            const int c = ymap[(size_t)perm_slot_host(wrap(m[1], P.N2), P.N2) * P.nslab + m[0] - m1min];
+            zslot[(size_t)perm_slot_host(wrap(m[2], P.N3), P.N3) * P.ldc + c] = g;
+        }
+        koffs[k].zslot = put(img, zslot);
+        koffs[k].ymap = put(img, ymap);
+        koffs[k].cpos = put(img, cpos);
+    }
+    // slots k / A of frequency k that stay empty for every point (ZeroBand of fft_device.hpp)
+    for (int ax = 0; ax < 3; ++ax) {
+        int A, B;
+        lds_split_host(p->fft[ax], &A, &B);
+        P.zero_band[ax] = true;
+        for (int64_t g = 0; g < P.npw_total; ++g) {
+            const int q = wrap(p->miller[3 * g + ax], p->fft[ax]) / A;
+            if (q >= B / 4 + 1 && q < B - (B + 3) / 4) P.zero_band[ax] = false;
+        }
+    }
     // LDS row of frequency i1 -> slab index
     std::vector<int> r2s(P.N1, -1);
     for (int s = 0; s < P.nslab; ++s) r2s[perm_slot_host(wrap(m1min + s, P.N1), P.N1)] = s;
     const size_t o_r2s = put(img, r2s);
+    std::vector<int> xrow(r2s);
+    for (int i = 0, absent = 0; i < P.N1; ++i)
+        if (r2s[i] < 0) xrow[i] = -1 - absent++;
+    const size_t o_xrow = put(img, xrow);
     // twiddles tw[jb*A + ka] = exp(+2 pi i jb ka / N), long double then rounded
     size_t o_tw64[3], o_tw32[3];
     for (int ax = 0; ax < 3; ++ax) {
@@ -324,18 +360,24 @@ int build_plan(const abacus_pw_problem *p, Plan &P, hipStream_t st) {
         K.row_off = reinterpret_cast<const int *>(at(koffs[k].row_off));
         K.row_list = reinterpret_cast<const int *>(at(koffs[k].row_list));
         K.kin = reinterpret_cast<const double *>(at(koffs[k].kin));
+        K.zslot = reinterpret_cast<const int *>(at(koffs[k].zslot));
+        K.ymap = reinterpret_cast<const unsigned short *>(at(koffs[k].ymap));
+        K.cpos = reinterpret_cast<const unsigned short *>(at(koffs[k].cpos));
+        K.ncol = (int)rows_list[k].size();
         K.kin32 = reinterpret_cast<const float *>(at(koffs[k].kin32));
     }
     {
         std::vector<KDesc> kd(p->nk);
         for (int k = 0; k < p->nk; ++k) {
             const KTables &K = P.k[k];
-            kd[k] = KDesc{K.pt_off, K.pt_g, K.pt_pos, K.row_off, K.row_list, K.kin, K.pw_off, K.npw, 0};
+            kd[k] = KDesc{K.pt_off, K.pt_g, K.pt_pos, K.row_off, K.row_list, K.kin, K.zslot, K.ymap, K.cpos, K.pw_off,
+                          K.npw, K.ncol};
         }
         APW_TRY(P.kdesc_buf.ensure(sizeof(KDesc) * kd.size()));
         APW_HIP(hipMemcpy(P.kdesc_buf.ptr, kd.data(), sizeof(KDesc) * kd.size(), hipMemcpyHostToDevice));
         P.kdesc = P.kdesc_buf.as<const KDesc>();
     }
+    P.xrow = reinterpret_cast<const int *>(at(o_xrow));
     P.row_to_slab = reinterpret_cast<const int *>(at(o_r2s));
     for (int ax = 0; ax < 3; ++ax) {
         P.tw64[ax] = at(o_tw64[ax]);

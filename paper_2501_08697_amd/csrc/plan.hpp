@@ -29,6 +29,14 @@ struct KTables {
     const int *row_list = nullptr;
     const double *kin = nullptr;   // |k+G|^2 in sphere order
     const float *kin32 = nullptr;
+    // z columns (the rows of every plane in order, column row_off[s] + r):
+    //   zslot [N3][ldc]   sphere index of slot perm3(i3) of a column, -1 where there is none
+    //   ymap [N2][nslab]  column of slot perm2(i2) in slab row s, 0xffff where there is none
+    const int *zslot = nullptr;
+    //   cpos [ldc]        slab row * (N2 | 1) + y slot of a column
+    const unsigned short *ymap = nullptr;
+    const unsigned short *cpos = nullptr;
+    int ncol = 0;
 };
 
 // The same tables as device-resident descriptors, one per k-point, so a single
@@ -40,9 +48,12 @@ struct KDesc {
     const int *row_off;
     const int *row_list;
     const double *kin;
+    const int *zslot;
+    const unsigned short *ymap;
+    const unsigned short *cpos;
     int64_t pw_off;
     int npw;
-    int pad;
+    int ncol;
 };
 
 struct DeviceBuffer {
@@ -61,6 +72,8 @@ struct Plan {
     int N1 = 0, N2 = 0, N3 = 0;
     int64_t N = 0;
     int nslab = 0, m1min = 0;
+    bool zero_band[3] = {};        // per axis: no k-point's sphere has a point in the codelet slots of ZeroBand
+    int max_ncol = 0, ldc = 0;     // most z columns of any k-point; row of the column buffer
     int max_rows = 0;              // most z-column rows in any plane of any k-point
     int nk = 0;
     std::vector<int> npw;
@@ -75,6 +88,7 @@ struct Plan {
     DeviceBuffer tables;          // all int/double geometry tables, one allocation
     DeviceBuffer kdesc_buf;       // KDesc[nk]
     const KDesc *kdesc = nullptr;
+    const int *xrow = nullptr;            // [N1]: slab index of x slot, or -1 - (rank among the slots without one)
     const int *row_to_slab = nullptr;     // [N1]: slab index of LDS row perm1(i1), or -1
     const void *tw64[3] = {nullptr, nullptr, nullptr};   // per axis, cx<double>[N_i]
     const void *tw32[3] = {nullptr, nullptr, nullptr};   // per axis, cx<float>[N_i]
@@ -109,6 +123,8 @@ struct Plan {
     bool force_tab_ready = false;
     DeviceBuffer force_stack; // [4 nproj][npw_k] complex128: beta, (k+G)_x beta, (k+G)_y beta, (k+G)_z beta
 };
+
+int lds_split_host(int n, int *a, int *b);   // the LDS split n = a b of a compiled length (local.hip)
 
 // Global tuning knobs (abacus_pw_set_tuning); 0 selects the library default.
 extern int g_band_batch;    // bands per local-term batch
