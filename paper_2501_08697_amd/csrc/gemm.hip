@@ -43,6 +43,7 @@ template <> struct Acc<float> {
 };
 
 constexpr int TM = 64, TN = 64, KT = 16, KP = KT + 1;
+constexpr int kMaxBatch = kGemmMaxBatch;   // products of one launch
 // Asking for at least two waves per SIMD makes the compiler keep the twelve
 // accumulator blocks in ordinary VGPRs (166 in FP64, three waves per SIMD)
 // instead of spreading them over VGPRs and AGPRs (278, one wave per SIMD).
@@ -57,10 +58,16 @@ constexpr int kGemmWaves = 2;
 // tiles that run at the same time read few distinct A and B tiles while they move
 // through K together (with the row tiles fastest, a chunk of a 2304 x 1024 product
 // kept all 36 A tiles in flight and read 15.7x the operands).
+// One launch covers up to kMaxBatch products of one shape M x N (the k-points of a call, whose
+// K = npw differ): grid z counts their splits one after the other.
+struct CnBatch {
+    int n;
+    int K[kMaxBatch], kchunk[kMaxBatch], z0[kMaxBatch + 1];   // z0[p]: first split of product p in grid z
+    int64_t lda[kMaxBatch], ldb[kMaxBatch], a[kMaxBatch], b[kMaxBatch];   // rows and element offsets of A and B
+};
 template <typename T, typename TS = T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_cn_part(int M, int N, int K, int kchunk, const cx<TS> *__restrict__ A,
-                                                      int64_t lda, const cx<TS> *__restrict__ B, int64_t ldb,
-                                                      cx<T> *__restrict__ part, int gm) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_cn_part(int M, int N, CnBatch bt, const cx<TS> *__restrict__ A,
+                                                      const cx<TS> *__restrict__ B, cx<T> *__restrict__ part, int gm) {
     __shared__ cx<T> As[TM][KP];
     __shared__ cx<T> Bs[TN][KP];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -70,8 +77,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     const int t = bx + nm * by;                        // tile of the chunk, in logical order
     const int grp = t / (gm * nn), first = grp * gm, rows = min(gm, nm - first);
     const int r = t - grp * gm * nn;
-    const int i0 = (first + r % rows) * TM, j0 = (r / rows) * TN, s = bz;
-    const int kb = s * kchunk, ke = min(K, kb + kchunk);
+    const int i0 = (first + r % rows) * TM, j0 = (r / rows) * TN;
+    int pb = 0;
+    while (pb + 1 < bt.n && bz >= bt.z0[pb + 1]) ++pb;
+    const int s = bz;   // the partial sums of the products follow each other
+    const int kb = (bz - bt.z0[pb]) * bt.kchunk[pb], ke = min(bt.K[pb], kb + bt.kchunk[pb]);
+    const int64_t lda = bt.lda[pb], ldb = bt.ldb[pb];
+    A += bt.a[pb];
+    B += bt.b[pb];
     using AV = typename Acc<T>::V;
     AV c1[2][2], c2[2][2], c3[2][2];   // sums of ar br, ai bi, (ar - ai)(br + bi)
 #pragma unroll
@@ -199,17 +212,23 @@ __host__ __device__ inline int reduce_groups(int M) {
     return M <= 0 ? 1 : std::max(1, std::min(kRedMaxGroups, std::min(kRedThreads / M, 4096 / M)));
 }
 
+struct RedBatch {
+    int z0[kMaxBatch + 1];   // splits [z0[p], z0[p + 1]) belong to product p
+};
 template <typename T>
-__global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, int nsplit, const cx<T> *__restrict__ part,
+__global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, RedBatch rb, const cx<T> *__restrict__ part,
                                                                int N, const double *__restrict__ dmat,
                                                                const int *__restrict__ blo, const int *__restrict__ bn,
                                                                const int *__restrict__ bdoff, cx<T> *__restrict__ P,
                                                                cx<T> *__restrict__ Q) {
     extern __shared__ __align__(16) unsigned char smem[];
     cx<double> *pl = reinterpret_cast<cx<double> *>(smem);   // [G][M] group sums, then the total in [0][M]
-    const int j = blockIdx.x;
+    const int j = blockIdx.x, pb = blockIdx.y, nsplit = rb.z0[pb + 1] - rb.z0[pb];
     const int G = reduce_groups(M);
     const int64_t sstride = (int64_t)N * M;
+    part += rb.z0[pb] * sstride;
+    Q += pb * sstride;
+    if (P) P += pb * sstride;
     for (int idx = threadIdx.x; idx < G * M; idx += blockDim.x) {
         const int g = idx / M, i = idx - g * M;
         const cx<T> *src = part + (int64_t)j * M + i;
@@ -255,16 +274,28 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, int nsplit
 // ----------------------------------------------------------------- NN ------
 // C[j][g] = alpha * sum_i A[j][i] B[i][g] + beta * C[j][g]
 // TS is the type A and B are stored in; they are rounded to T while staged.
+// One launch covers up to kMaxBatch products of one M and K (the k-points of a call, whose G =
+// npw differ): grid y counts their column tiles one after the other.
+struct NnBatch {
+    int n;
+    int G[kMaxBatch], y0[kMaxBatch + 1];   // y0[p]: first column tile of product p in grid y
+    int64_t ldb[kMaxBatch], ldc[kMaxBatch], a[kMaxBatch], b[kMaxBatch], c[kMaxBatch];   // rows, element offsets
+};
 template <typename T, typename TC, typename TS = T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_nn(int M, int G, int K, const cx<TS> *__restrict__ A, int64_t lda,
-                                                 const cx<TS> *__restrict__ B, int64_t ldb, cx<TC> *__restrict__ C,
-                                                 int64_t ldc, double alpha, double beta) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_nn(int M, int K, NnBatch bt, const cx<TS> *__restrict__ A, int64_t lda,
+                                                 const cx<TS> *__restrict__ B, cx<TC> *__restrict__ C, double alpha, double beta) {
     __shared__ cx<T> As[TM][KP];
     __shared__ cx<T> Bs[KT][TN + 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     int bx, by, bz;
     xcd_block(bx, by, bz);   // the row tiles of one column block share an L2
-    const int j0 = bx * TM, g0 = by * TN;
+    int pb = 0;
+    while (pb + 1 < bt.n && by >= bt.y0[pb + 1]) ++pb;
+    const int j0 = bx * TM, g0 = (by - bt.y0[pb]) * TN, G = bt.G[pb];
+    const int64_t ldb = bt.ldb[pb], ldc = bt.ldc[pb];
+    A += bt.a[pb];
+    B += bt.b[pb];
+    C += bt.c[pb];
     using AV = typename Acc<T>::V;
     AV c1[2][2], c2[2][2], c3[2][2];   // sums of ar br, ai bi, (ar + ai)(br + bi)
 #pragma unroll
@@ -367,18 +398,26 @@ __global__ void k_grad_d(int nb, int M, const cx<T> *__restrict__ P, const cx<T>
 }
 
 // ------------------------------------------------------------ launchers ----
-// Default K chunk: at least 512 work-groups, chunks of at most 1024 (a K chunk of
-// A and B read by every tile of the chunk stays in the caches, where one long K
-// range per tile streams A once per column of tiles from HBM: at 2304 x 1024 x
-// 161,235 the projection read 13.7x its operands with one split, measured with
-// FETCH_SIZE), but no more splits than keep the partial sums under kPartCap bytes.
+// Default K chunk of `batch` products in one launch: at least 512 work-groups, chunks of at
+// most 1024 (a K chunk of A and B read by every tile of the chunk stays in the caches, where
+// one long K range per tile streams A once per column of tiles from HBM: at 2304 x 1024 x
+// 161,235 the projection read 13.7x its operands with one split, measured with FETCH_SIZE),
+// but no more splits than keep the partial sums under kPartCap bytes. A work-group spends about
+// 2 us on a stage of 16 k when few others run, so small products are split down to chunks of
+// 32: 32 x 16 x 1503 took 33.5 us in chunks of 256 (6 work-groups of 16 stages), 13.0 in chunks
+// of 64 and 9.3 in chunks of 32. 768 work-groups (three a CU) gained nothing at 256 x 128 x
+// 23,847: 87.4 us and 12.8 us of reduction against 84.9 and 11.0.
+// `wide` is the rule of the reduced-precision products whose sums feed complex128 results
+// (chunks of at least 256): the chunk groups their FP32 sums, so it stays.
 constexpr size_t kPartCap = size_t(1) << 30;
-static int splits_for(int M, int N, int K, int chunk_hint, int *chunk) {
-    const int tiles = ceil_div(M, TM) * ceil_div(N, TN);
+static int splits_wanted(int M, int N, int batch) {
+    const int tiles = ceil_div(M, TM) * ceil_div(N, TN) * batch;
+    return std::max(1, 512 / std::max(1, tiles));
+}
+static int splits_for(int M, int N, int K, int chunk_hint, int batch, bool wide, int *chunk) {
     int c = chunk_hint > 0 ? chunk_hint : 0;
     if (c <= 0) {
-        const int want = std::max(1, 512 / std::max(1, tiles));
-        c = std::min(1024, std::max(256, ceil_div(K, want)));
+        c = std::min(1024, std::max(wide ? 256 : 32, ceil_div(K, splits_wanted(M, N, batch))));
         const int64_t max_splits = std::max<int64_t>(1, (int64_t)(kPartCap / ((size_t)M * N * 16)));
         c = std::max<int64_t>(c, ceil_div64(K, max_splits));
     }
@@ -387,30 +426,45 @@ static int splits_for(int M, int N, int K, int chunk_hint, int *chunk) {
     return std::max(1, ceil_div(K, c));
 }
 
-// Upper bound over every K' <= K: the split count grows with K up to the cap (with
-// a chunk hint without one).
+// Upper bound over every M' <= M, N' <= N, K' <= K and either rule. A product has either chunks
+// of 1024 (or the capped or hinted length), or at most 512 / tiles splits of at least 32 k, and
+// tiles * 64 * 64 >= M' N'.
 size_t gemm_cn_part_bytes(int M, int N, int K, int elem_bytes, int chunk_hint) {
-    int c;
-    int ns = splits_for(M, N, K, chunk_hint, &c);
-    if (chunk_hint <= 0) ns = std::max(ns, std::max(1, 512 / std::max(1, ceil_div(M, TM) * ceil_div(N, TN))));
-    return (size_t)ns * M * N * elem_bytes;
+    const size_t mn = (size_t)M * N;
+    if (chunk_hint > 0) return (size_t)ceil_div(K, ceil_div(chunk_hint, KT) * KT) * mn * elem_bytes;
+    const size_t few = std::max(mn, std::min((size_t)ceil_div(K, 1024) * mn, kPartCap / 16));
+    const size_t many = std::min<size_t>((size_t)512 * TM * TN, (size_t)ceil_div(K, 32) * mn);
+    return std::max(few, many) * elem_bytes;
+}
+
+int gemm_batch_limit(int M, int N, int K, int elem_bytes, int chunk_hint) {
+    return (int)std::max<size_t>(1, std::min<size_t>(kMaxBatch, kPartCap / gemm_cn_part_bytes(M, N, K, elem_bytes, chunk_hint)));
 }
 
 template <typename T, typename TS = T>
-static int cn_part(int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *part,
-                   int chunk_hint, int *nsplit, hipStream_t st) {
-    int chunk;
-    const int ns = splits_for(M, N, K, chunk_hint, &chunk);
-    *nsplit = ns;
-    dim3 grid(ceil_div(M, TM), ceil_div(N, TN), ns);
+static int cn_part(int M, int N, const CnProduct *pr, int np, const void *A, const void *B, void *part,
+                   int chunk_hint, bool wide, RedBatch *rb, hipStream_t st) {
+    CnBatch bt;
+    bt.n = np;
+    bt.z0[0] = 0;
+    for (int i = 0; i < np; ++i) {
+        bt.K[i] = pr[i].K;
+        bt.z0[i + 1] = bt.z0[i] + splits_for(M, N, pr[i].K, chunk_hint, np, wide, &bt.kchunk[i]);
+        bt.lda[i] = pr[i].lda;
+        bt.ldb[i] = pr[i].ldb;
+        bt.a[i] = pr[i].a;
+        bt.b[i] = pr[i].b;
+    }
+    for (int i = 0; i <= np; ++i) rb->z0[i] = bt.z0[i];
+    dim3 grid(ceil_div(M, TM), ceil_div(N, TN), bt.z0[np]);
     // group of row tiles: about one XCD's resident work-groups (32 CUs x 3) per group;
     // a chunk of at most two such groups keeps the row tiles fastest (one group): at
     // 864 x 512 per k-point that order measured 1-2% faster than groups of 12 rows
     const int tiles = (int)(grid.x * grid.y);
     const int gm = tiles <= 192 ? (int)grid.x : std::max(1, std::min((int)grid.x, 96 / (int)grid.y));
     KernelTimer kt("gemm_cn", st);
-    hipLaunchKernelGGL((k_gemm_cn_part<T, TS>), grid, dim3(256), 0, st, M, N, K, chunk, static_cast<const cx<TS> *>(A),
-                       lda, static_cast<const cx<TS> *>(B), ldb, static_cast<cx<T> *>(part), gm);
+    hipLaunchKernelGGL((k_gemm_cn_part<T, TS>), grid, dim3(256), 0, st, M, N, bt, static_cast<const cx<TS> *>(A),
+                       static_cast<const cx<TS> *>(B), static_cast<cx<T> *>(part), gm);
     return check_launch("gemm_cn");
 }
 
@@ -419,11 +473,12 @@ template <typename T, typename TS = T>
 static int gemm_cn_t(int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                      int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st) {
     if (M <= 0 || N <= 0) return ABACUS_PW_OK;
-    int ns;
-    APW_TRY((cn_part<T, TS>(M, N, K, A, lda, B, ldb, part, chunk_hint, &ns, st)));
+    RedBatch rb;
+    const CnProduct pr{K, lda, ldb, 0, 0};
+    APW_TRY((cn_part<T, TS>(M, N, &pr, 1, A, B, part, chunk_hint, sizeof(T) < sizeof(TS), &rb, st)));
     const int64_t tot = (int64_t)M * N;
     KernelTimer kt("gemm_reduce", st);
-    hipLaunchKernelGGL((k_reduce<T, TS>), dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, M, N, ns,
+    hipLaunchKernelGGL((k_reduce<T, TS>), dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, M, N, rb.z0[1],
                        static_cast<const cx<T> *>(part), static_cast<cx<TS> *>(C), ldc, alpha, beta);
     return check_launch("gemm_reduce");
 }
@@ -450,38 +505,65 @@ int gemm_cn(int prec, int M, int N, int K, const void *A, int64_t lda, const voi
 }
 
 template <typename T>
-static int proj_dapply_t(int M, int N, int K, const void *Bm, int64_t ldb, const void *psi, int64_t ldp,
+static int proj_dapply_t(int M, int N, const CnProduct *pr, int np, const void *Bm, const void *psi,
                          const double *dmat, const int *blo, const int *bn, const int *bdoff, void *P, void *Q,
-                         void *part, int chunk_hint, hipStream_t st) {
+                         void *part, int chunk_hint, bool wide, hipStream_t st) {
     if (M <= 0 || N <= 0) return ABACUS_PW_OK;
-    int ns;
-    APW_TRY(cn_part<T>(M, N, K, Bm, ldb, psi, ldp, part, chunk_hint, &ns, st));
+    RedBatch rb;
+    APW_TRY(cn_part<T>(M, N, pr, np, Bm, psi, part, chunk_hint, wide, &rb, st));
     const size_t lds = (size_t)reduce_groups(M) * M * sizeof(cx<double>);
     if (lds > 64 * 1024) return set_error(ABACUS_PW_EBAD_SHAPE, "too many projectors for the D-apply stage");
     KernelTimer kt("reduce_dapply", st);
-    hipLaunchKernelGGL(k_reduce_dapply<T>, dim3(N), dim3(kRedThreads), lds, st, M, ns, static_cast<const cx<T> *>(part), N,
+    hipLaunchKernelGGL(k_reduce_dapply<T>, dim3(N, np), dim3(kRedThreads), lds, st, M, rb, static_cast<const cx<T> *>(part), N,
                        dmat, blo, bn, bdoff, static_cast<cx<T> *>(P), static_cast<cx<T> *>(Q));
     return check_launch("reduce_dapply");
 }
 
-int proj_dapply(int prec, int M, int N, int K, const void *Bm, int64_t ldb, const void *psi, int64_t ldp,
+int proj_dapply(int prec, int M, int N, const CnProduct *pr, int np, const void *Bm, const void *psi,
                 const double *dmat, const int *blo, const int *bn, const int *bdoff, void *P, void *Q, void *part,
-                int chunk_hint, hipStream_t st) {
-    return prec == 0 ? proj_dapply_t<double>(M, N, K, Bm, ldb, psi, ldp, dmat, blo, bn, bdoff, P, Q, part,
-                                             chunk_hint, st)
-                     : proj_dapply_t<float>(M, N, K, Bm, ldb, psi, ldp, dmat, blo, bn, bdoff, P, Q, part,
-                                            chunk_hint, st);
+                int chunk_hint, bool wide, hipStream_t st) {
+    return prec == 0 ? proj_dapply_t<double>(M, N, pr, np, Bm, psi, dmat, blo, bn, bdoff, P, Q, part, chunk_hint, wide,
+                                             st)
+                     : proj_dapply_t<float>(M, N, pr, np, Bm, psi, dmat, blo, bn, bdoff, P, Q, part, chunk_hint, wide,
+                                            st);
+}
+
+template <typename T, typename TC, typename TS = T>
+static int gemm_nn_batch_t(int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
+                           void *C, double alpha, double beta, hipStream_t st) {
+    if (M <= 0) return ABACUS_PW_OK;
+    NnBatch bt;
+    bt.n = np;
+    bt.y0[0] = 0;
+    for (int i = 0; i < np; ++i) {
+        bt.G[i] = pr[i].G;
+        bt.y0[i + 1] = bt.y0[i] + ceil_div(pr[i].G, TN);
+        bt.ldb[i] = pr[i].ldb;
+        bt.ldc[i] = pr[i].ldc;
+        bt.a[i] = pr[i].a;
+        bt.b[i] = pr[i].b;
+        bt.c[i] = pr[i].c;
+    }
+    if (bt.y0[np] == 0) return ABACUS_PW_OK;
+    dim3 grid(ceil_div(M, TM), bt.y0[np]);
+    KernelTimer kt("gemm_nn", st);
+    hipLaunchKernelGGL((k_gemm_nn<T, TC, TS>), grid, dim3(256), 0, st, M, K, bt, static_cast<const cx<TS> *>(A), lda,
+                       static_cast<const cx<TS> *>(B), static_cast<cx<TC> *>(C), alpha, beta);
+    return check_launch("gemm_nn");
+}
+
+int gemm_nn_batch(int prec, int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
+                  void *C, double alpha, double beta, hipStream_t st) {
+    return prec == 0 ? gemm_nn_batch_t<double, double>(M, K, pr, np, A, lda, B, C, alpha, beta, st)
+                     : gemm_nn_batch_t<float, float>(M, K, pr, np, A, lda, B, C, alpha, beta, st);
 }
 
 template <typename T, typename TC, typename TS = T>
 static int gemm_nn_t(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                      int64_t ldc, double alpha, double beta, hipStream_t st) {
     if (M <= 0 || G <= 0) return ABACUS_PW_OK;
-    dim3 grid(ceil_div(M, TM), ceil_div(G, TN));
-    KernelTimer kt("gemm_nn", st);
-    hipLaunchKernelGGL((k_gemm_nn<T, TC, TS>), grid, dim3(256), 0, st, M, G, K, static_cast<const cx<TS> *>(A), lda,
-                       static_cast<const cx<TS> *>(B), ldb, static_cast<cx<TC> *>(C), ldc, alpha, beta);
-    return check_launch("gemm_nn");
+    const NnProduct pr{G, ldb, ldc, 0, 0, 0};
+    return gemm_nn_batch_t<T, TC, TS>(M, K, &pr, 1, A, lda, B, C, alpha, beta, st);
 }
 
 int gemm_nn_f32_of_f64(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
@@ -505,7 +587,10 @@ int reduce_dapply_f32(int M, int N, int nsplit, const void *part, const double *
     const size_t lds = (size_t)reduce_groups(M) * M * sizeof(cx<double>);
     if (lds > 64 * 1024) return set_error(ABACUS_PW_EBAD_SHAPE, "too many projectors for the D-apply stage");
     KernelTimer kt("reduce_dapply", st);
-    hipLaunchKernelGGL(k_reduce_dapply<float>, dim3(N), dim3(kRedThreads), lds, st, M, nsplit, static_cast<const c32 *>(part),
+    RedBatch rb;
+    rb.z0[0] = 0;
+    rb.z0[1] = nsplit;
+    hipLaunchKernelGGL(k_reduce_dapply<float>, dim3(N), dim3(kRedThreads), lds, st, M, rb, static_cast<const c32 *>(part),
                        N, dmat, blo, bn, bdoff, static_cast<c32 *>(nullptr), static_cast<c32 *>(Q));
     return check_launch("reduce_dapply");
 }

@@ -12,11 +12,27 @@ size_t gemm_cn_part_bytes(int M, int N, int K, int elem_bytes, int chunk_hint);
 int gemm_cn(int prec, int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
             int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st);
 
-// P[j][i] = <beta_i | psi_j> (M = nproj, N = bands, K = npw); Q[j][i] = sum_t D_blk(i) P[j][.].
-// P may be NULL. D-block tables as in the plan.
-int proj_dapply(int prec, int M, int N, int K, const void *Bm, int64_t ldb, const void *psi, int64_t ldp,
+// Products of one launch, one per k-point of a call: their inner (or outer) length and rows,
+// and where their operands start (elements from the launch's base pointers).
+constexpr int kGemmMaxBatch = 8;
+struct CnProduct {
+    int K;
+    int64_t lda, ldb, a, b;
+};
+struct NnProduct {
+    int G;
+    int64_t ldb, ldc, a, b, c;
+};
+// Products of that shape (K at most) one launch may take: kGemmMaxBatch, and partial sums of at
+// most 1 GiB (gemm_cn_part_bytes each).
+int gemm_batch_limit(int M, int N, int K, int elem_bytes, int chunk_hint);
+
+// For every product p: P[j][i] = <beta_i | psi_j> (M = nproj, N = bands, K = npw);
+// Q[j][i] = sum_t D_blk(i) P[j][.], P and Q [np][N][M]. P may be NULL. D-block tables as in the
+// plan. wide: the K chunks of the mixed modes.
+int proj_dapply(int prec, int M, int N, const CnProduct *pr, int np, const void *Bm, const void *psi,
                 const double *dmat, const int *blo, const int *bn, const int *bdoff, void *P, void *Q, void *part,
-                int chunk_hint, hipStream_t st);
+                int chunk_hint, bool wide, hipStream_t st);
 
 // C[j*ldc + g] = alpha * sum_i A[j*lda + i] B[i*ldb + g] + beta * C[...],  j < M, g < G.
 // gemm_cn on complex128 A, B, C with FP32 products: the operands are rounded to
@@ -24,6 +40,10 @@ int proj_dapply(int prec, int M, int N, int K, const void *Bm, int64_t ldb, cons
 // (the subspace projection of the reduced-precision Davidson phase).
 int gemm_cn_f32_of_f64(int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                        int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st);
+
+// The same for np products: A [M][lda], B rows of ldb, C rows of ldc, from their offsets.
+int gemm_nn_batch(int prec, int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
+                  void *C, double alpha, double beta, hipStream_t st);
 
 int gemm_nn(int prec, int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
             int64_t ldc, double alpha, double beta, hipStream_t st);

@@ -118,6 +118,14 @@ int order(hipEvent_t e, hipStream_t from, hipStream_t to) {
 // follows there as soon as that batch's local term is done, so the GEMMs share
 // the GPU with the plane passes. Off by default: on the 72^3 / 23847-PW case the
 // concurrent kernels slow each other down about as much as they overlap.
+// The projector GEMMs of several k-points share a launch (as many as keep the partial sums
+// bounded): 7 atoms x 9 projectors, 37 bands at three k-points ran three launches of 35 to
+// 138 work-groups each. MIXED_FP32 stages one k-point's psi at a time.
+static int proj_batch(const Plan &P, int prec, int nb, int k0, int k1) {
+    if (prec == ABACUS_PW_MIXED_FP32 || prec == ABACUS_PW_MIXED_BF16) return 1;
+    return std::min(k1 - k0, gemm_batch_limit(P.nproj, nb, P.max_npw, prec == ABACUS_PW_FP64 ? 16 : 8, g_splitk_chunk));
+}
+
 // Bytes of the per-call work buffers of apply_h_range for nb bands at [k0, k1) (current knobs).
 void hwork_sizes(const Plan &P, int prec, int nb, int k0, int k1, size_t sz[kHWorkParts]) {
     const bool bf = prec == ABACUS_PW_MIXED_BF16;
@@ -133,7 +141,7 @@ void hwork_sizes(const Plan &P, int prec, int nb, int k0, int k1, size_t sz[kHWo
         sz[3] = sizeof(uint32_t) * (size_t)nb * bf16_ld(P.max_npw);
         sz[4] = sizeof(uint32_t) * (size_t)nb * bf16_ld(P.nproj);
     } else {
-        sz[2] = gemm_cn_part_bytes(P.nproj, nb, P.max_npw, (int)gb, g_splitk_chunk);
+        sz[2] = gemm_cn_part_bytes(P.nproj, nb, P.max_npw, (int)gb, g_splitk_chunk) * proj_batch(P, prec, nb, k0, k1);
     }
     if (prec == ABACUS_PW_MIXED_FP32) sz[5] = (size_t)nb * P.max_npw * 8;
 }
@@ -194,7 +202,8 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
                               : static_cast<const void *>(P.beta32.as<char>() + (size_t)P.nproj * K.pw_off * 8);
     };
     // Q_k = D B_k^H psi_k
-    for (int k = k0; k < k1; ++k) {
+    const int kbatch = proj_batch(P, prec, nb, k0, k1);
+    for (int k = k0; k < k1; k += kbatch) {
         const KTables &K = P.k[k];
         const char *xk = static_cast<const char *>(psi) + (size_t)nb * (K.pw_off - P.pw_off[k0]) * ib;
         void *qk_ptr = static_cast<char *>(projq) + qk * (k - k0);
@@ -207,17 +216,26 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
             continue;
         }
         const void *xg = xk;
-        if (prec == ABACUS_PW_MIXED_FP32) {
+        const bool mixed = prec == ABACUS_PW_MIXED_FP32;
+        if (mixed) {
             APW_TRY(convert_f64_to_f32(2 * (int64_t)nb * K.npw, reinterpret_cast<const double *>(xk),
                                        static_cast<float *>(tmp_io), gs));
             xg = tmp_io;
         }
-        APW_TRY(proj_dapply(gemm_prec, P.nproj, nb, K.npw, bk, K.npw, xg, K.npw, p.dmat, P.proj_blk_lo, P.proj_blk_n,
-                            P.proj_blk_doff, nullptr, qk_ptr, gemm_part, g_splitk_chunk, gs));
+        CnProduct pr[kGemmMaxBatch];
+        const int np = std::min(kbatch, k1 - k);
+        for (int i = 0; i < np; ++i) {
+            const KTables &Ki = P.k[k + i];
+            const int64_t o = Ki.pw_off - K.pw_off;
+            pr[i] = CnProduct{Ki.npw, Ki.npw, Ki.npw, o * P.nproj, o * nb};
+        }
+        APW_TRY(proj_dapply(gemm_prec, P.nproj, nb, pr, np, bk, xg, p.dmat, P.proj_blk_lo, P.proj_blk_n,
+                            P.proj_blk_doff, nullptr, qk_ptr, gemm_part, g_splitk_chunk, mixed, gs));
     }
     // hpsi[b0 .. b0+bbt) += B_k Q_k[b0 .. b0+bbt) for every k-point
     auto add_bq = [&](int b0, int bbt, hipStream_t s) -> int {
-        for (int k = k0; k < k1; ++k) {
+        const int step = bf || prec == ABACUS_PW_MIXED_FP32 ? 1 : kGemmMaxBatch;
+        for (int k = k0; k < k1; k += step) {
             const KTables &K = P.k[k];
             char *yk = static_cast<char *>(hpsi) + ((size_t)nb * (K.pw_off - P.pw_off[k0]) + (size_t)b0 * K.npw) * ib;
             const char *qb = static_cast<char *>(projq) + qk * (k - k0) + (size_t)b0 * P.nproj * gb;
@@ -230,8 +248,17 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
             }
             else if (prec == ABACUS_PW_MIXED_FP32)
                 APW_TRY(gemm_nn_f32_into_f64(bbt, K.npw, P.nproj, qb, P.nproj, bk, K.npw, yk, K.npw, 1.0, 1.0, s));
-            else
-                APW_TRY(gemm_nn(gemm_prec, bbt, K.npw, P.nproj, qb, P.nproj, bk, K.npw, yk, K.npw, 1.0, 1.0, s));
+            else {
+                NnProduct pr[kGemmMaxBatch];
+                const int np = std::min(step, k1 - k);
+                for (int i = 0; i < np; ++i) {
+                    const KTables &Ki = P.k[k + i];
+                    const int64_t o = Ki.pw_off - K.pw_off;
+                    pr[i] = NnProduct{Ki.npw, Ki.npw, Ki.npw, (int64_t)i * nb * P.nproj, o * P.nproj,
+                                      o * nb + (int64_t)b0 * (Ki.npw - K.npw)};
+                }
+                APW_TRY(gemm_nn_batch(gemm_prec, bbt, P.nproj, pr, np, qb, P.nproj, bk, yk, 1.0, 1.0, s));
+            }
         }
         return ABACUS_PW_OK;
     };
