@@ -730,9 +730,9 @@ def c4_times(B, W, dev, davidson=True):
 
 
 def force_times(B, W, dev, prob, dp, x, steps):
-    """Nonlocal force on the 64 atoms of the benchmark cell from its 128 bands, FP64: one
-    stacking pass over beta, one GEMM [B; (k+G)_x B; (k+G)_y B; (k+G)_z B]^H psi
-    (8 (4 nproj) nb npw flops), one reduction per atom."""
+    """Nonlocal force on the 64 atoms of the benchmark cell from its 128 bands, FP64: the
+    projection B^H psi (8 nproj nb npw flops), one product of the same size contracted with
+    beta and k+G in its epilogue, one reduction per atom."""
     import torch
     occ = torch.from_numpy(W.band_weights(prob, 0)).to(dev)
     for _ in range(2):
@@ -750,7 +750,7 @@ def force_times(B, W, dev, prob, dp, x, steps):
     kern = B.profile_read()
     ms = a.elapsed_time(b) / steps
     npw = int(prob.npw[0])
-    flops = 8.0 * 4 * prob.nproj * prob.nb * npw
+    flops = 8.0 * prob.nproj * prob.nb * npw
     rows = {name: {"launches_per_call": n / steps, "avg_ms": tot / n} for name, (n, tot) in kern.items()}
     res = {"ms_per_call_with_kernel_events": ms, "gemm_flops": flops, "kernels": rows}
     if "gemm_cn" in rows:

@@ -378,6 +378,108 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
         }
 }
 
+// --------------------------------------------------------------- force -----
+// X[i][g] = sum_n W[n][i] psi[n][g] (the NN product with a transposed A), contracted in the
+// epilogue: part[tile][i][al] = sum over the tile's g of kg[g][al] Im(beta[i][g] conj(X[i][g])).
+// X is never stored: the product and one read of beta, where projecting (k+G)_al psi as well
+// took four projections' worth of products and a stacked copy of beta.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_force_contract(
+    int M, int G, int nb, const z64 *__restrict__ W, const z64 *__restrict__ psi, const z64 *__restrict__ beta,
+    const double *__restrict__ kg, double *__restrict__ part) {
+    using A = Acc<double>;
+    __shared__ z64 As[TM][KP];
+    __shared__ z64 Bs[KT][TN + 1];
+    __shared__ double red[2][TM][3];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int bx, by, bz;
+    xcd_block(bx, by, bz);   // the row tiles of one column block share an L2
+    const int i0 = bx * TM, g0 = by * TN;
+    d4 c1[2][2], c2[2][2], c3[2][2];   // sums of ar br, ai bi, (ar + ai)(br + bi)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) c1[a][b] = c2[a][b] = c3[a][b] = A::zero();
+    const int wi = (w & 1) * 32, wg = (w >> 1) * 32;
+    const int lk = tid >> 4, lc = (tid & 15) * 4;   // loader of both: row n, 4 consecutive i or g
+    z64 ra[4], rb[4];
+    auto load = [&](int k0) {
+        const int n = k0 + lk;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ra[q] = n < nb && i0 + lc + q < M ? W[(int64_t)n * M + i0 + lc + q] : z64{0.0, 0.0};
+            rb[q] = n < nb && g0 + lc + q < G ? psi[(int64_t)n * G + g0 + lc + q] : z64{0.0, 0.0};
+        }
+    };
+    load(0);
+    for (int k0 = 0; k0 < nb; k0 += KT) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            As[lc + q][lk] = ra[q];
+            Bs[lk][lc + q] = rb[q];
+        }
+        __syncthreads();
+        if (k0 + KT < nb) load(k0 + KT);   // next stage in flight while this one multiplies
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int kk = 4 * q + (lane >> 4);
+            z64 a[2], b[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) a[r] = As[wi + 16 * r + (lane & 15)][kk];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) b[c] = Bs[kk][wg + 16 * c + (lane & 15)];
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    c1[r][c] = A::mma(a[r].re, b[c].re, c1[r][c]);
+                    c2[r][c] = A::mma(a[r].im, b[c].im, c2[r][c]);
+                    c3[r][c] = A::mma(a[r].re + a[r].im, b[c].re + b[c].im, c3[r][c]);
+                }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int li = wi + 16 * r + A::row(lane, e), gi = i0 + li;
+            double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int gg = g0 + wg + 16 * c + (lane & 15);
+                if (gi < M && gg < G) {
+                    const z64 b = beta[(int64_t)gi * G + gg];
+                    const double p1 = c1[r][c][e], p2 = c2[r][c][e], p3 = c3[r][c][e];
+                    const double t = b.im * (p1 - p2) - b.re * (p3 - p1 - p2);
+#pragma unroll
+                    for (int al = 0; al < 3; ++al) s[al] += kg[3 * (int64_t)gg + al] * t;
+                }
+            }
+#pragma unroll
+            for (int al = 0; al < 3; ++al) {
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1) s[al] += __shfl_xor(s[al], o, 16);
+                if ((lane & 15) == 0) red[w >> 1][li][al] = s[al];
+            }
+        }
+    __syncthreads();
+    for (int t = tid; t < TM * 3; t += 256) {
+        const int li = t / 3, al = t - 3 * li;
+        if (i0 + li < M) part[((int64_t)by * M + i0 + li) * 3 + al] = red[0][li][al] + red[1][li][al];
+    }
+}
+
+int force_contract_tiles(int G) { return ceil_div(G, TN); }
+
+int force_contract(int M, int G, int nb, const void *W, const void *psi, const void *beta, const double *kg,
+                   double *part, hipStream_t st) {
+    KernelTimer kt("force_contract", st);
+    hipLaunchKernelGGL(k_force_contract, dim3(ceil_div(M, TM), ceil_div(G, TN)), dim3(256), 0, st, M, G, nb,
+                       static_cast<const z64 *>(W), static_cast<const z64 *>(psi), static_cast<const z64 *>(beta), kg,
+                       part);
+    return check_launch("force_contract");
+}
+
 // grad_d[blk(i)][i - lo][t] (+)= sum_n Re(Q[n][i] conj(P[n][lo + t])), one thread per projector i.
 template <typename T>
 __global__ void k_grad_d(int nb, int M, const cx<T> *__restrict__ P, const cx<T> *__restrict__ Q,

@@ -58,6 +58,13 @@ int gemm_nn_f32_of_f64(int M, int G, int K, const void *A, int64_t lda, const vo
 int gemm_nn_f32_into_f64(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                          int64_t ldc, double alpha, double beta, hipStream_t st);
 
+// part[tile][i][al] = sum over the tile's g of kg[g][al] Im(beta[i][g] conj(X[i][g])) with
+// X[i][g] = sum_n W[n][i] psi[n][g]: W [nb][M], psi [nb][G], beta [M][G], kg [G][3]; tiles of
+// g = force_contract_tiles(G).
+int force_contract_tiles(int G);
+int force_contract(int M, int G, int nb, const void *W, const void *psi, const void *beta, const double *kg,
+                   double *part, hipStream_t st);
+
 // grad_d entry (i, lo+t) of each atom block (+)= sum_n Re(Q[n][i] conj(P[n][lo+t])); P, Q are [nb][M].
 int grad_d_accumulate(int prec, int nb, int M, const void *P, const void *Q, const int *blo, const int *bn,
                       const int *bdoff, double *gd, int first, hipStream_t st);

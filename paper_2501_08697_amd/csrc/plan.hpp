@@ -121,7 +121,6 @@ struct Plan {
     DeviceBuffer cheb[3];     // Chebyshev recurrence: two polynomial terms and H applied to one
     DeviceBuffer force_tab;   // nonlocal force: (k+G) [npw_total][3] float64, then atom offsets [natom+1]
     bool force_tab_ready = false;
-    DeviceBuffer force_stack; // [4 nproj][npw_k] complex128: beta, (k+G)_x beta, (k+G)_y beta, (k+G)_z beta
 };
 
 int lds_split_host(int n, int *a, int *b);   // the LDS split n = a b of a compiled length (local.hip)
