@@ -38,8 +38,6 @@ SCRATCH_ALLOWED = {
     # exceeds LDS at FP64, the compact-row kernel runs instead)
     "_ZN3apw8k_yz_fwdILi120EddE": 128,
     "_ZN3apw8k_yz_fwdILi128EddE": 256,
-    # tridiagonal reduction with its panel in global memory (subspace above 256): 8 bytes
-    "_ZN3apw7k_hetrdILb0EE": 16,
 }
 
 

@@ -9,7 +9,8 @@
 //   k_trinv      the inverse L^{-1} (one wavefront per column).
 //   k_hetrd      Householder reduction of a Hermitian matrix to a real
 //                symmetric tridiagonal T = Q^H A Q (one work-group, blocked in
-//                panels; the reflector convention H = I - tau v v^H, v[0] = 1,
+//                panels, orders below kTrdMulti; trd_multi of dense_large.hip from
+//                there on; the reflector convention H = I - tau v v^H, v[0] = 1,
 //                makes every off-diagonal real).
 //   k_stebz      eigenvalues of T by bisection on Sturm counts; one wavefront per
 //                eigenvalue, each of its 64 lanes evaluating one point of a
@@ -190,7 +191,11 @@ __global__ __launch_bounds__(256) void k_trinv(int n, const z64 *__restrict__ L,
 
 constexpr int kPanel = 8;   // columns per panel of the blocked reduction
 constexpr int kRows = 64;   // rows per LDS chunk of the trailing update
-constexpr int kPanelLdsN = 256;   // largest n whose panel vectors V, W are kept in LDS
+// Orders from here on take one launch per column over many compute units (trd_multi): the
+// launches cost 8 us a column whatever the order, one compute unit's pass over the trailing
+// matrix grows with it. Measured, one compute unit / many: n = 64 356 / 495 us, 128 857 / 1013,
+// 192 1695 / 1587, 256 2956 / 2161.
+constexpr int kTrdMulti = 176;
 constexpr int kSymvBatch = 8;    // loads in flight per thread in the symmetric product
 
 // A (n x n, ld) Hermitian, full storage. On exit d[n], e[n-1] hold T and
@@ -199,27 +204,22 @@ constexpr int kSymvBatch = 8;    // loads in flight per thread in the symmetric 
 // (n x n) receives the same v_k in columns k+1 .. n-1 (contiguous, for k_unmtr).
 //
 // Blocked as in LAPACK's panel reduction: inside a panel of kPanel columns the
-// rank-2 updates A -= v w^H + w v^H are kept as the vectors V, W (VW scratch,
-// 2 kPanel n) and applied to each column as it is reached; the symmetric
+// rank-2 updates A -= v w^H + w v^H are kept as the vectors V, W (in LDS) and applied to each column as it is reached; the symmetric
 // product y = A22 v reads A22 as it was before the panel and subtracts
 // V (W^H v) + W (V^H v); the trailing matrix takes all the panel's updates in
 // one pass. Since v = [1, scale * x] is linear in the reflector's scale, the
 // product and the dot products with V and W start from the raw column x in the
 // same pass as its norm, leaving four barriers per column.
-template <bool kLdsPanel>
-__global__ __launch_bounds__(kNT) void k_hetrd(int n, z64 *A, int ld, double *d, double *e, z64 *tau, z64 *VW,
-                                               z64 *Vr) {
-    __shared__ z64 xs[kSmallSub];      // column k from the diagonal down, panel updates applied
-    __shared__ z64 a0s[kSmallSub];     // first column of A22 (conjugated row)
+__global__ __launch_bounds__(kNT) void k_hetrd(int n, z64 *A, int ld, double *d, double *e, z64 *tau, z64 *Vr) {
+    __shared__ z64 xs[kTrdMulti];      // column k from the diagonal down, panel updates applied
+    __shared__ z64 a0s[kTrdMulti];     // first column of A22 (conjugated row)
     __shared__ z64 part[kNT];          // partial sums of A22 x
     __shared__ z64 dots[2 * kPanel];   // W^H x, V^H x over rows k+2 ..
     __shared__ z64 ybc;                // y_0, for the next column's update
     __shared__ double red[kNT / 64], red2[2][kNT / 64];
     __shared__ z64 rowvw[2 * kPanel][kRows];   // V then W, rows r0 .. r0 + kRows of the trailing update
-    __shared__ z64 vw_lds[kLdsPanel ? 2 * kPanel * kPanelLdsN : 1];
+    __shared__ z64 Vp[2 * kPanel * kTrdMulti];   // column q of the panel at [q * n + row], V then W
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = kNT / 64;
-    // column q of the panel at [q * n + row]; in LDS (n <= kPanelLdsN) or in VW
-    z64 *Vp = kLdsPanel ? vw_lds : VW;
     z64 *Wp = Vp + (int64_t)kPanel * n;
     for (int k0 = 0; k0 < n - 1; k0 += kPanel) {
         const int bw = min(kPanel, n - 1 - k0);
@@ -749,12 +749,15 @@ int stein_vectors(int n, const double *d, const double *e, int nw, const double 
     return check_launch("stein");
 }
 
-// Small orders: d, e (n doubles each), tau (n), the panel vectors V, W of the tridiagonal
-// reduction (2 kPanel n), the reflector rows Vr (n x n), Z (n x n doubles) and the
+size_t trd_scratch_elems(int n);   // dense_large.hip
+int trd_multi(int n, z64 *A, int ld, double *d, double *e, z64 *tau, z64 *Vr, z64 *work, hipStream_t st);
+
+// Small orders: d, e (n doubles each), tau (n), the panel vectors of the tridiagonal
+// reduction (trd_scratch_elems), the reflector rows Vr (n x n), Z (n x n doubles) and the
 // inverse-iteration arrays (6 n S doubles). Large orders: the layout of dense_large.hip.
 size_t heev_scratch_bytes(int n) {
     if (n >= kLargeHeevMin) return heev_large_scratch_bytes(n, n) + stein_work_bytes(n, n) + 256;
-    return (size_t)n * (2 * sizeof(double) + sizeof(z64)) + (size_t)2 * kPanel * n * sizeof(z64) +
+    return (size_t)n * (2 * sizeof(double) + sizeof(z64)) + trd_scratch_elems(n) * sizeof(z64) +
            (size_t)n * n * sizeof(z64) + (size_t)n * n * sizeof(double) + stein_work_bytes(n, n) + 1024;
 }
 
@@ -765,14 +768,14 @@ int heev_lowest(int n, z64 *A, int ld, int nw, double *w, z64 *coef, int ldc, vo
     double *d = reinterpret_cast<double *>(s);
     double *e = d + n;
     z64 *tau = reinterpret_cast<z64 *>(e + n);
-    z64 *VW = tau + n;
-    z64 *Vr = VW + (size_t)2 * kPanel * n;
+    z64 *panel = tau + n;
+    z64 *Vr = panel + trd_scratch_elems(n);
     double *Z = reinterpret_cast<double *>(Vr + (size_t)n * n);
     double *work = Z + (size_t)n * n;
     {
         KernelTimer kt("hetrd", st);
-        if (n <= kPanelLdsN) hipLaunchKernelGGL(k_hetrd<true>, dim3(1), dim3(kNT), 0, st, n, A, ld, d, e, tau, VW, Vr);
-        else hipLaunchKernelGGL(k_hetrd<false>, dim3(1), dim3(kNT), 0, st, n, A, ld, d, e, tau, VW, Vr);
+        if (n >= kTrdMulti) APW_TRY(trd_multi(n, A, ld, d, e, tau, Vr, panel, st));
+        else hipLaunchKernelGGL(k_hetrd, dim3(1), dim3(kNT), 0, st, n, A, ld, d, e, tau, Vr);
         APW_TRY(check_launch("hetrd"));
     }
     APW_TRY(stebz_values(n, d, e, nw, w, st));

@@ -6,18 +6,18 @@
 // updates run on the MFMA GEMMs.
 //
 // Tridiagonal reduction T = Q^H A Q (LAPACK's blocked scheme, restated): columns
-// are reduced in panels of kPL. For column k of a panel (c = k - k0):
-//   k_trd_col   (one work-group) finishes the previous column's w vector
-//               (w = y - tau/2 (y^H v) v), forms column k as stored minus the
-//               panel's rank-2 updates so far (A - V W^H - W V^H), builds the
-//               Householder reflector H = I - tau v v^H (v[k+1] = 1, real
-//               off-diagonal beta) and the dot products W^H v, V^H v;
-//   k_trd_hemv  (m / 4 work-groups, one wavefront per row) y = tau (A22 v -
-//               V (W^H v) - W (V^H v)) with A22 the trailing matrix as it was
-//               when the panel started, read row by row (coalesced, Hermitian
-//               full storage).
-// After the panel the trailing matrix takes all its updates at once,
-// A22 -= [V W] [W V]^H, one complex GEMM with K = 2 kPL on the matrix cores.
+// are reduced in panels of PL. One launch per column k = k0 + c (k_trd_step): every
+// work-group finishes the previous column's w vector (w = y - tau/2 (y^H v) v), forms
+// column k as stored minus the panel's rank-2 updates so far (A - V W^H - W V^H), its
+// Householder reflector H = I - tau v v^H (v[k+1] = 1, real off-diagonal beta) and the dot
+// products W^H v, V^H v, all of which is O(n PL) and done alike in each; then it computes
+// its own rows of y = tau (A22 v - V (W^H v) - W (V^H v)), A22 the trailing matrix as it
+// was when the panel started. The matrix rows are fetched at the start, behind the vector
+// work. After the panel the trailing matrix takes its updates at once (k_trd_update).
+// What bounds it is the chain of launches, each waiting on the one before: a column took
+// 11.5 us at n = 256 in one work-group and 20.1 us at n = 1024 in two launches (one
+// work-group for the vectors, then the product), 8.3 and 12.7 us now. The panel's rows staged in
+// LDS at the start measured the same (8.3 and 12.7); panels of 16 spill.
 //
 // Back-transformation coef = Q Z (Z the real tridiagonal eigenvectors): the
 // reflectors, kept as rows of Vr, are applied in blocks of kPL from the last to
@@ -37,8 +37,7 @@ namespace apw {
 
 namespace {
 
-constexpr int kPL = 32;       // columns per panel of the tridiagonal reduction (and reflectors per WY block)
-constexpr int kColThreads = 1024;
+constexpr int kPL = 32;       // reflectors per WY block of the back-transformation
 constexpr int kCB = 64;       // columns per block of the blocked Cholesky
 
 __device__ __forceinline__ z64 zc(z64 a) { return z64{a.re, -a.im}; }
@@ -50,222 +49,241 @@ __device__ __forceinline__ double wsum(double v) {
     return v;
 }
 
-// Sum over the work-group (fixed order).
-__device__ double bsum(double v, double *red) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    v = wsum(v);
-    __syncthreads();
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int i = 0; i < nw; ++i) s += red[i];
-    return s;
-}
-
-// Panel buffers: PX row i = [V[i][0..kPL) | W[i][0..kPL)], PY row i = [W | V].
 struct TrdArgs {
     int n, ld;
     z64 *A;
     double *d, *e;
     z64 *tau;
     z64 *Vr;      // [n][n] reflector rows (zero outside k+1 .. n-1)
-    z64 *PX, *PY; // [n][2 kPL]
-    z64 *PXc;     // [2 kPL][n]: PX by columns, so that reads over rows are coalesced
-    z64 *vbuf;    // [n] current reflector, contiguous
-    z64 *y;       // [n] tau (A22 v - ...) of the current column
-    z64 *s;       // [2 kPL]: W^H v then V^H v
+    z64 *P;       // [2 PL][n] panel vectors by columns: V_0 .. V_{PL-1}, W_0 .. W_{PL-1}
+    z64 *y;       // [2][n] y of the current column and of the one before (by parity of k)
 };
 
-// mode 0: finish w of panel column c-1 (if c > 0), then reduce column k = k0 + c.
-// mode 1: only finish w of panel column c-1 (end of a panel).
-__global__ __launch_bounds__(kColThreads) void k_trd_col(TrdArgs a, int k0, int c, int mode) {
-    __shared__ z64 wl[kMaxSub];    // w of panel column c-1, rows k ..
-    __shared__ z64 al[kMaxSub];    // column k, rows k ..
-    __shared__ double red[kColThreads / 64];
-    __shared__ z64 zred[2][kColThreads / 64];
-    const int n = a.n, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = kColThreads / 64;
-    const int k = k0 + c;   // column to reduce (mode 0); w of column k - 1 is finished first
+// Sum over the work-group of one complex value per thread (fixed order); one barrier.
+template <int NT> __device__ __forceinline__ z64 zsum(z64 v, z64 *red) {
+    const double re = wsum(v.re), im = wsum(v.im);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = z64{re, im};
+    __syncthreads();
+    z64 s = z64{0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < NT / 64; ++q) s = s + red[q];
+    return s;
+}
+
+constexpr int kTrdRows = 2;    // rows of y per wavefront
+constexpr int kTrdAhead = 4;   // 64-column pieces of a row fetched ahead
+
+template <int NT, int PL>
+__global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0, int c) {
+    extern __shared__ __align__(16) unsigned char smem_trd[];
+    const int n = a.n, k = k0 + c, m = n - k;
+    z64 *xs = reinterpret_cast<z64 *>(smem_trd);   // [m] column k, rows k ..
+    z64 *wl = xs + m;                              // [m] w of panel column c - 1, rows k ..
+    __shared__ z64 pk[2 * PL];                     // row k of V and W
+    __shared__ z64 dots[2 * PL];                   // W^H x, V^H x over rows k + 2 ..
+    __shared__ z64 zred[NT / 64];
+    __shared__ double red[NT / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const z64 *V = a.P, *W = a.P + (int64_t)PL * n;
+    // this wavefront's rows of A22 and their panel rows
+    const int r0 = k + 1 + (blockIdx.x * (NT / 64) + wv) * kTrdRows;
+    z64 ar[kTrdRows][kTrdAhead], a0[kTrdRows], vr[kTrdRows], wr[kTrdRows];
+    const int lq = min(lane, max(c - 1, 0));
+#pragma unroll
+    for (int r = 0; r < kTrdRows; ++r) {
+        const int i = min(r0 + r, n - 1);
+        const z64 *row = a.A + (int64_t)i * a.ld;
+#pragma unroll
+        for (int u = 0; u < kTrdAhead; ++u) ar[r][u] = row[min(k + 2 + lane + 64 * u, n - 1)];
+        a0[r] = row[k + 1];
+        vr[r] = V[(int64_t)lq * n + i];
+        wr[r] = W[(int64_t)lq * n + i];
+    }
+    if (tid < 2 * PL && tid % PL < c) pk[tid] = a.P[(int64_t)tid * n + k];
+    // w of column c - 1 over rows k .. (row k = its reflector's leading 1)
+    z64 wk = z64{0.0, 0.0};   // w at row k
     if (c > 0) {
-        // w = y + alpha v over rows kp + 1 .. n - 1, kp = k - 1, alpha = -tau/2 (y^H v)
-        const int kp = k - 1;
-        double pr = 0.0, pi = 0.0;
-        for (int i = kp + 1 + tid; i < n; i += kColThreads) {
-            const z64 yv = a.y[i], v = a.vbuf[i];
-            pr += yv.re * v.re + yv.im * v.im;   // conj(y) v
-            pi += yv.re * v.im - yv.im * v.re;
+        const z64 *yp = a.y + (int64_t)((k - 1) & 1) * n, *vp = V + (int64_t)(c - 1) * n;
+        z64 s = z64{0.0, 0.0};
+        for (int i = tid; i < m; i += NT) {
+            const z64 yv = yp[k + i], v = vp[k + i];
+            wl[i] = yv;
+            xs[i] = v;
+            s = s + cmulc(v, yv);   // conj(y) v
         }
-        pr = wsum(pr);
-        pi = wsum(pi);
-        __syncthreads();
-        if (lane == 0) {
-            zred[0][wv] = z64{pr, 0.0};
-            zred[1][wv] = z64{pi, 0.0};
-        }
-        __syncthreads();
-        double sr = 0.0, si = 0.0;
-        for (int q = 0; q < nwv; ++q) {
-            sr += zred[0][q].re;
-            si += zred[1][q].re;
-        }
-        const z64 t = a.tau[kp];
-        const z64 al2 = cmul(z64{-0.5 * t.re, -0.5 * t.im}, z64{sr, si});
-        for (int i = kp + 1 + tid; i < n; i += kColThreads) {
-            const z64 w = a.y[i] + cmul(al2, a.vbuf[i]);
+        const z64 yk = yp[k], t = a.tau[k - 1];
+        s = zsum<NT>(s, zred);
+        const z64 al = cmul(z64{-0.5 * t.re, -0.5 * t.im}, s);
+        for (int i = tid; i < m; i += NT) {
+            const z64 w = wl[i] + cmul(al, xs[i]);
             wl[i] = w;
-            a.PX[(int64_t)i * 2 * kPL + kPL + (c - 1)] = w;
-            a.PY[(int64_t)i * 2 * kPL + (c - 1)] = w;
-            a.PXc[(int64_t)(kPL + c - 1) * n + i] = w;
+            if (blockIdx.x == 0) a.P[(int64_t)(PL + c - 1) * n + k + i] = w;
         }
-        __syncthreads();
+        wk = yk + al;
     }
-    if (mode == 1) return;
-    // row k of the panel (V then W), the same for every row below
-    __shared__ z64 pk[2 * kPL];
-    if (tid < c) {
-        pk[tid] = a.PXc[(int64_t)tid * n + k];
-        pk[kPL + tid] = tid == c - 1 ? wl[k] : a.PXc[(int64_t)(kPL + tid) * n + k];
-    }
-    __syncthreads();
-    // column k, rows k .. n-1: conj(row k of A) minus the panel's updates of columns q < c
-    // (the panel read by columns: consecutive threads, consecutive rows)
-    // Eight columns' values are loaded before any is used, so their latencies overlap; the
-    // index is clamped to c - 1 (a valid address) and values beyond c are not used. Column
-    // c - 1 of W is being written by this kernel: its values come from wl instead.
-    for (int i = k + tid; i < n; i += kColThreads) {
-        z64 x = zc(a.A[(int64_t)k * a.ld + i]);
-        for (int q0 = 0; q0 < c; q0 += 8) {
-            z64 vi[8], wi[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = min(q0 + u, c - 1);
-                vi[u] = a.PXc[(int64_t)q * n + i];
-                wi[u] = a.PXc[(int64_t)(kPL + q) * n + i];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = q0 + u;
-                if (q < c) {
-                    const z64 w = q == c - 1 ? wl[i] : wi[u];
-                    x = x - cmulc(vi[u], pk[kPL + q]) - cmulc(w, pk[q]);   // v_i conj(w_k) + w_i conj(v_k)
-                }
-            }
-        }
-        al[i] = x;
-    }
-    __syncthreads();
-    // reflector from x = al[k+1 ..]
+    // column k, rows k ..: conj(row k of A) minus the panel's updates of columns q < c.
+    // The panel values are loaded before any is used (clamped to column c - 1, whose W
+    // comes from wl: this launch is writing it).
     double p = 0.0;
-    for (int i = k + 2 + tid; i < n; i += kColThreads) p += za2(al[i]);
-    const double xn2 = bsum(p, red);
-    const z64 alpha = al[k + 1];
-    __syncthreads();   // every thread holds alpha before al[k+1] is overwritten below
+    for (int i = tid; i < m; i += NT) {
+        z64 x = zc(a.A[(int64_t)k * a.ld + k + i]);
+        if (c > 0) {
+            z64 vi[PL], wi[PL];
+#pragma unroll
+            for (int q = 0; q < PL; ++q) {
+                vi[q] = V[(int64_t)min(q, c - 1) * n + k + i];
+                wi[q] = W[(int64_t)max(min(q, c - 2), 0) * n + k + i];
+            }
+#pragma unroll
+            for (int q = 0; q < PL; ++q)
+                if (q < c) {
+                    const z64 w = q == c - 1 ? wl[i] : wi[q];
+                    const z64 wq = q == c - 1 ? wk : pk[PL + q];
+                    x = x - cmulc(vi[q], wq) - cmulc(w, pk[q]);   // v_i conj(w_k) + w_i conj(v_k)
+                }
+        }
+        xs[i] = x;
+        if (i >= 2) p += za2(x);
+    }
+    p = wsum(p);
+    if (lane == 0) red[wv] = p;
+    __syncthreads();
+    // W^H x and V^H x over rows k + 2 .., one wavefront per product
+    for (int q2 = wv; q2 < 2 * c; q2 += NT / 64) {
+        const bool isw = q2 < c;
+        const int q = isw ? q2 : q2 - c;
+        const bool from_wl = isw && q == c - 1;
+        const z64 *col = (isw ? W : V) + (int64_t)q * n + k;
+        z64 s = z64{0.0, 0.0};
+        for (int i = 2 + lane; i < m; i += 256) {   // four rows per lane in flight
+            z64 u[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int ii = min(i + 64 * r, m - 1);
+                u[r] = from_wl ? wl[ii] : col[ii];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (i + 64 * r < m) s = s + cmulc(xs[i + 64 * r], u[r]);   // conj(u) x
+        }
+        const double sr = wsum(s.re), si = wsum(s.im);
+        if (lane == 0) dots[(isw ? 0 : PL) + q] = z64{sr, si};
+    }
+    __syncthreads();
+    double xn2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NT / 64; ++q) xn2 += red[q];
+    const z64 alpha = xs[1];
     double beta = alpha.re;
     z64 t = z64{0.0, 0.0}, scale = z64{0.0, 0.0};
     if (!(xn2 == 0.0 && alpha.im == 0.0)) {
         beta = -copysign(sqrt(alpha.re * alpha.re + alpha.im * alpha.im + xn2), alpha.re);
         t = z64{(beta - alpha.re) / beta, -alpha.im / beta};
-        const z64 den = z64{alpha.re - beta, alpha.im};
+        const z64 den = z64{alpha.re - beta, alpha.im};   // scale = 1 / (alpha - beta)
         const double dd = za2(den);
         scale = z64{den.re / dd, -den.im / dd};
     }
-    if (tid == 0) {
-        a.d[k] = al[k].re;
-        a.e[k] = beta;
-        a.tau[k] = t;
-    }
-    for (int i = tid; i < n; i += kColThreads) {
-        z64 v = z64{0.0, 0.0};
-        if (i == k + 1) v = z64{1.0, 0.0};
-        else if (i > k + 1) v = cmul(al[i], scale);
-        a.Vr[(int64_t)k * n + i] = v;
-        if (i > k) {
-            a.vbuf[i] = v;
-            al[i] = v;   // al now holds v
-            a.PX[(int64_t)i * 2 * kPL + c] = v;
-            a.PY[(int64_t)i * 2 * kPL + kPL + c] = v;
-            a.PXc[(int64_t)c * n + i] = v;
+    if (blockIdx.x == 0) {
+        if (tid == 0) {
+            a.d[k] = xs[0].re;
+            a.e[k] = beta;
+            a.tau[k] = t;
+        }
+        for (int i = tid; i < n; i += NT) {
+            z64 v = z64{0.0, 0.0};
+            if (i == k + 1) v = z64{1.0, 0.0};
+            else if (i > k + 1) v = cmul(xs[i - k], scale);
+            a.Vr[(int64_t)k * n + i] = v;
+            if (i > k) a.P[(int64_t)c * n + i] = v;
         }
     }
-    __syncthreads();
-    // W^H v and V^H v over rows k+1 .. for the panel columns q < c (one wave per dot product)
-    for (int q2 = wv; q2 < 2 * c; q2 += nwv) {
-        const bool isw = q2 < c;
-        const int q = isw ? q2 : q2 - c;
-        const bool from_wl = isw && q == c - 1;   // the W column this kernel wrote
-        const z64 *col = a.PXc + (int64_t)(isw ? kPL + q : q) * n;
-        double sr = 0.0, si = 0.0;
-        int i = k + 1 + lane;
-        for (; i + 192 < n; i += 256) {   // four rows per lane in flight
-            z64 u[4];
+    // y = tau (A22 v - V (W^H v) - W (V^H v)) for the wavefront's rows, v = [1, scale x];
+    // lane q < c takes the panel column q of the correction
+    z64 wd = z64{0.0, 0.0}, vd = z64{0.0, 0.0};   // W_q^H v, V_q^H v
+    if (lane < c) {
+        const z64 w1 = lane == c - 1 ? wl[1] : W[(int64_t)lane * n + k + 1];
+        wd = zc(w1) + cmul(scale, dots[lane]);
+        vd = zc(V[(int64_t)lane * n + k + 1]) + cmul(scale, dots[PL + lane]);
+    }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) u[r] = from_wl ? wl[i + 64 * r] : col[i + 64 * r];
+    for (int r = 0; r < kTrdRows; ++r) {
+        const int i = r0 + r;
+        if (i >= n) break;
+        const z64 *row = a.A + (int64_t)i * a.ld + k;
+        z64 s = z64{0.0, 0.0};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const z64 pr = cmulc(al[i + 64 * r], u[r]);   // conj(u) v
-                sr += pr.re;
-                si += pr.im;
-            }
+        for (int u = 0; u < kTrdAhead; ++u) {
+            const int j = 2 + lane + 64 * u;
+            if (j < m) s = s + cmul(ar[r][u], xs[j]);
         }
-        for (; i < n; i += 64) {
-            const z64 u = from_wl ? wl[i] : col[i];
-            const z64 pr = cmulc(al[i], u);
-            sr += pr.re;
-            si += pr.im;
+        for (int j = 2 + lane + 64 * kTrdAhead; j < m; j += 256) {
+            z64 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = row[min(j + 64 * u, m - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (j + 64 * u < m) s = s + cmul(v[u], xs[j + 64 * u]);
         }
-        sr = wsum(sr);
-        si = wsum(si);
-        if (lane == 0) a.s[(isw ? 0 : kPL) + q] = z64{sr, si};
+        s = cmul(scale, s);
+        if (lane < c) s = s - cmul(vr[r], wd) - cmul(lane == c - 1 ? wl[i - k] : wr[r], vd);
+        const double sr = wsum(s.re), si = wsum(s.im);
+        if (lane == 0) a.y[(int64_t)(k & 1) * n + i] = cmul(t, a0[r] + z64{sr, si});
     }
 }
 
-// y[i] = tau (sum_j A[i][j] v[j] - sum_q V[i][q] s_w[q] - W[i][q] s_v[q]) for rows i > k, j > k.
-// v is staged in LDS (dynamic, (n - k - 1) values, vl[j - k - 1] = v[j]).
-__global__ __launch_bounds__(256) void k_trd_hemv(TrdArgs a, int k, int c) {
-    extern __shared__ __align__(16) unsigned char smem_hemv[];
-    z64 *vl = reinterpret_cast<z64 *>(smem_hemv) - (k + 1);
-    const int n = a.n, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int j = k + 1 + threadIdx.x; j < n; j += blockDim.x) vl[j] = a.vbuf[j];
+// Trailing update after a panel of bw columns, A[i][j] -= sum_q V_iq conj(W_jq) + W_iq conj(V_jq)
+// for i, j >= t0 = k0 + bw (full storage; entries (i, j) and (j, i) come out exactly conjugate).
+// The last w of the panel is finished here, by every work-group for its own rows and columns.
+// A work-group takes 32 rows x 64 columns; a thread one column and eight rows.
+template <int PL>
+__global__ __launch_bounds__(256) void k_trd_update(TrdArgs a, int k0, int bw) {
+    __shared__ z64 rv[PL][32], rw[PL][32];
+    __shared__ z64 zred[4];
+    const int n = a.n, t0 = k0 + bw, kp = t0 - 1, tid = threadIdx.x;
+    const int i0 = t0 + blockIdx.y * 32, j = t0 + blockIdx.x * 64 + (tid & 63);
+    const z64 *V = a.P, *W = a.P + (int64_t)PL * n, *yp = a.y + (int64_t)(kp & 1) * n;
+    const z64 *vl = V + (int64_t)(bw - 1) * n;
+    z64 s = z64{0.0, 0.0};
+    for (int i = t0 + tid; i < n; i += 256) s = s + cmulc(vl[i], yp[i]);   // conj(y) v
+    const z64 t = a.tau[kp];
+    s = zsum<256>(s, zred);
+    const z64 al = cmul(z64{-0.5 * t.re, -0.5 * t.im}, s);
+    for (int q = tid >> 5; q < PL; q += 8) {
+        const int r = tid & 31, i = min(i0 + r, n - 1), qc = min(q, bw - 1);
+        const z64 v = V[(int64_t)qc * n + i], w = q == bw - 1 ? yp[i] + cmul(al, v) : W[(int64_t)qc * n + i];
+        rv[q][r] = q < bw ? v : z64{0.0, 0.0};
+        rw[q][r] = q < bw ? w : z64{0.0, 0.0};
+    }
+    z64 vj[PL], wj[PL];
+    const int jc = min(j, n - 1);
+#pragma unroll
+    for (int q = 0; q < PL; ++q) {
+        const int qc = min(q, bw - 1);
+        const z64 v = V[(int64_t)qc * n + jc], w = q == bw - 1 ? yp[jc] + cmul(al, v) : W[(int64_t)qc * n + jc];
+        vj[q] = q < bw ? zc(v) : z64{0.0, 0.0};
+        wj[q] = q < bw ? zc(w) : z64{0.0, 0.0};
+    }
     __syncthreads();
-    const int i = k + 1 + blockIdx.x * 4 + wv;
-    if (i >= n) return;
-    const z64 *row = a.A + (int64_t)i * a.ld;
-    double sr = 0.0, si = 0.0;
-    int j = k + 1 + lane;
-    for (; j + 192 < n; j += 256) {
-        z64 r[4];
+    if (j >= n) return;
+    z64 x[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = row[j + 64 * u];
+    for (int u = 0; u < 8; ++u) x[u] = a.A[(int64_t)min(i0 + (tid >> 6) + 4 * u, n - 1) * a.ld + j];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const z64 pr = cmul(r[u], vl[j + 64 * u]);
-            sr += pr.re;
-            si += pr.im;
+    for (int u = 0; u < 8; ++u) {
+        const int r = (tid >> 6) + 4 * u;
+        if (i0 + r >= n) break;
+        z64 s0 = z64{0.0, 0.0}, s1 = z64{0.0, 0.0};   // two independent chains
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            s0 = s0 + cmul(rv[q][r], wj[q]);
+            s1 = s1 + cmul(rw[q][r], vj[q]);
         }
+        a.A[(int64_t)(i0 + r) * a.ld + j] = x[u] - (s0 + s1);
     }
-    for (; j < n; j += 64) {
-        const z64 pr = cmul(row[j], vl[j]);
-        sr += pr.re;
-        si += pr.im;
-    }
-    // panel corrections: lane q < c takes V[i][q] s_w[q] + W[i][q] s_v[q]
-    if (lane < c) {
-        const z64 *px = a.PX + (int64_t)i * 2 * kPL;
-        const z64 cr = cmul(px[lane], a.s[lane]) + cmul(px[kPL + lane], a.s[kPL + lane]);
-        sr -= cr.re;
-        si -= cr.im;
-    }
-    sr = wsum(sr);
-    si = wsum(si);
-    if (lane == 0) a.y[i] = cmul(a.tau[k], z64{sr, si});
 }
 
 __global__ void k_trd_last(const z64 *A, int ld, int n, double *d) {
     if (threadIdx.x == 0 && blockIdx.x == 0) d[n - 1] = A[(int64_t)(n - 1) * ld + n - 1].re;
-}
-
-__global__ void k_zero(z64 *p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = z64{0.0, 0.0};
 }
 
 // coef[j][i] = Z[j][i] (real eigenvector rows to complex rows of ld ldc)
@@ -371,19 +389,57 @@ __global__ __launch_bounds__(1024) void k_chol_diag(z64 *G, int ld, int j0, int 
 
 // ------------------------------------------------------------------ drivers --
 
+constexpr int kTrdPanel = 8;
+template <int NT, int PL> static int trd_panel_step(const TrdArgs &a, int k0, int c, hipStream_t st) {
+    static bool once = false;
+    if (!once) {
+        APW_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_trd_step<NT, PL>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024));
+        once = true;
+    }
+    const int m = a.n - k0 - c;
+    hipLaunchKernelGGL((k_trd_step<NT, PL>), dim3((unsigned)ceil_div(m - 1, NT / 64 * kTrdRows)), dim3(NT),
+                       2 * sizeof(z64) * (size_t)m, st, a, k0, c);
+    return ABACUS_PW_OK;
+}
+
+template <int PL> static int trd_reduce(const TrdArgs &a, hipStream_t st) {
+    for (int k0 = 0; k0 < a.n - 1; k0 += PL) {
+        const int bw = std::min(PL, a.n - 1 - k0);
+        for (int c = 0; c < bw; ++c) {
+            // a thread per element of the vectors, up to 512: 1024 leave 128 registers and spill
+            if (a.n - k0 - c <= 256) APW_TRY((trd_panel_step<256, PL>(a, k0, c, st)));
+            else APW_TRY((trd_panel_step<512, PL>(a, k0, c, st)));
+        }
+        const int mt = a.n - k0 - bw;
+        hipLaunchKernelGGL((k_trd_update<PL>), dim3((unsigned)ceil_div(mt, 64), (unsigned)ceil_div(mt, 32)), dim3(256),
+                           0, st, a, k0, bw);
+        APW_TRY(check_launch("hetrd panel"));
+    }
+    return ABACUS_PW_OK;
+}
+
+size_t trd_scratch_elems(int n) { return (size_t)(2 * kTrdPanel + 2) * n; }   // P and y
+
+// A -> d[n], e[n - 1], tau[n], Vr [n][n]; work: trd_scratch_elems(n) complex128. A is destroyed.
+int trd_multi(int n, z64 *A, int ld, double *d, double *e, z64 *tau, z64 *Vr, z64 *work, hipStream_t st) {
+    TrdArgs a{n, ld, A, d, e, tau, Vr, work, work + (size_t)2 * kTrdPanel * n};
+    APW_TRY(trd_reduce<kTrdPanel>(a, st));
+    hipLaunchKernelGGL(k_trd_last, dim3(1), dim3(64), 0, st, A, ld, n, d);
+    return check_launch("hetrd last");
+}
+
 // Scratch of the large-order routines (bytes), carved in the order below.
 size_t heev_large_scratch_bytes(int n, int nw) {
     const size_t zn = sizeof(z64);
-    return 17 * 256                                       // alignment of the 17 regions
+    return 12 * 256                                       // alignment of the regions
            + (size_t)n * (2 * sizeof(double) + zn)        // d, e, tau
            + (size_t)n * n * zn                           // Vr
-           + (size_t)3 * n * 2 * kPL * zn                 // PX, PY, PXc
-           + (size_t)2 * n * zn + 2 * kPL * zn            // vbuf, y, s
+           + trd_scratch_elems(n) * zn                    // panel vectors, y
            + (size_t)n * n * sizeof(double)               // Z
            + (size_t)2 * kPL * kPL * zn                   // Gram, T
            + (size_t)2 * nw * kPL * zn                    // S, S'
-           + std::max(gemm_cn_part_bytes(n, n, 2 * kPL, 16, 0), gemm_cn_part_bytes(kPL, nw, n, 16, 0))
-           + 4096;
+           + gemm_cn_part_bytes(kPL, nw, n, 16, 0) + 4096;
 }
 
 int stein_vectors(int n, const double *d, const double *e, int nw, const double *w, double *Z, int ldz, void *work,
@@ -400,57 +456,26 @@ int heev_lowest_large(int n, z64 *A, int ld, int nw, double *w, z64 *coef, int l
         p += (bytes + 255) / 256 * 256;
         return q;
     };
-    TrdArgs a;
-    a.n = n;
-    a.ld = ld;
-    a.A = A;
-    a.d = reinterpret_cast<double *>(take(sizeof(double) * n));
-    a.e = reinterpret_cast<double *>(take(sizeof(double) * n));
-    a.tau = reinterpret_cast<z64 *>(take(sizeof(z64) * n));
-    a.Vr = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)n * n));
-    a.PX = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)n * 2 * kPL));
-    a.PY = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)n * 2 * kPL));
-    a.PXc = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)n * 2 * kPL));
-    a.vbuf = reinterpret_cast<z64 *>(take(sizeof(z64) * n));
-    a.y = reinterpret_cast<z64 *>(take(sizeof(z64) * n));
-    a.s = reinterpret_cast<z64 *>(take(sizeof(z64) * 2 * kPL));
+    double *d = reinterpret_cast<double *>(take(sizeof(double) * n));
+    double *e = reinterpret_cast<double *>(take(sizeof(double) * n));
+    z64 *tau = reinterpret_cast<z64 *>(take(sizeof(z64) * n));
+    z64 *Vr = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)n * n));
+    z64 *trd = reinterpret_cast<z64 *>(take(sizeof(z64) * trd_scratch_elems(n)));
     double *Z = reinterpret_cast<double *>(take(sizeof(double) * (size_t)n * n));
     z64 *Gt = reinterpret_cast<z64 *>(take(sizeof(z64) * kPL * kPL));
     z64 *T = reinterpret_cast<z64 *>(take(sizeof(z64) * kPL * kPL));
     z64 *S = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)nw * kPL));
     z64 *Sp = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)nw * kPL));
-    void *part = take(std::max(gemm_cn_part_bytes(n, n, 2 * kPL, 16, 0), gemm_cn_part_bytes(kPL, nw, n, 16, 0)));
+    void *part = take(gemm_cn_part_bytes(kPL, nw, n, 16, 0));
     {
         KernelTimer kt("hetrd_mc", st);
-        for (int k0 = 0; k0 < n - 1; k0 += kPL) {
-            const int bw = std::min(kPL, n - 1 - k0);
-            if (bw < kPL) {
-                // a partial panel: the columns it does not write must be zero for the trailing GEMM
-                const int64_t cnt = (int64_t)n * 2 * kPL;
-                hipLaunchKernelGGL(k_zero, dim3((unsigned)ceil_div64(cnt, 256)), dim3(256), 0, st, a.PX, cnt);
-                hipLaunchKernelGGL(k_zero, dim3((unsigned)ceil_div64(cnt, 256)), dim3(256), 0, st, a.PY, cnt);
-            }
-            for (int c = 0; c < bw; ++c) {
-                const int k = k0 + c, m = n - k - 1;
-                hipLaunchKernelGGL(k_trd_col, dim3(1), dim3(kColThreads), 0, st, a, k0, c, 0);
-                hipLaunchKernelGGL(k_trd_hemv, dim3((unsigned)ceil_div(m, 4)), dim3(256), sizeof(z64) * (size_t)m, st, a,
-                                   k, c);
-            }
-            hipLaunchKernelGGL(k_trd_col, dim3(1), dim3(kColThreads), 0, st, a, k0, bw, 1);
-            APW_TRY(check_launch("hetrd_mc panel"));
-            const int t0 = k0 + bw, mt = n - t0;
-            if (mt > 0)
-                APW_TRY(gemm_cn(0, mt, mt, 2 * kPL, a.PY + (size_t)t0 * 2 * kPL, 2 * kPL, a.PX + (size_t)t0 * 2 * kPL,
-                                2 * kPL, A + (size_t)t0 * ld + t0, ld, -1.0, 1.0, part, 0, st));
-        }
-        hipLaunchKernelGGL(k_trd_last, dim3(1), dim3(64), 0, st, A, ld, n, a.d);
-        APW_TRY(check_launch("hetrd_mc last"));
+        APW_TRY(trd_multi(n, A, ld, d, e, tau, Vr, trd, st));
     }
-    APW_TRY(stebz_values(n, a.d, a.e, nw, w, st));
+    APW_TRY(stebz_values(n, d, e, nw, w, st));
     {
         // inverse-iteration work space: its own region after the GEMM partials
         void *work = take(stein_work_bytes(n, nw));
-        APW_TRY(stein_vectors(n, a.d, a.e, nw, w, Z, n, work, stein_work_bytes(n, nw), st));
+        APW_TRY(stein_vectors(n, d, e, nw, w, Z, n, work, stein_work_bytes(n, nw), st));
     }
     KernelTimer kt("unmtr_mc", st);
     {
@@ -462,9 +487,9 @@ int heev_lowest_large(int n, z64 *A, int ld, int nw, double *w, z64 *coef, int l
     const int nref = n - 1;
     for (int b0 = ((nref - 1) / kPL) * kPL; b0 >= 0; b0 -= kPL) {
         const int nbk = std::min(kPL, nref - b0);
-        const z64 *Vb = a.Vr + (size_t)b0 * n;
+        const z64 *Vb = Vr + (size_t)b0 * n;
         APW_TRY(gemm_cn(0, nbk, nbk, n, Vb, n, Vb, n, Gt, nbk, 1.0, 0.0, part, 0, st));
-        hipLaunchKernelGGL(k_wy_t, dim3(1), dim3(kPL), 0, st, nbk, a.tau + b0, Gt, T);
+        hipLaunchKernelGGL(k_wy_t, dim3(1), dim3(kPL), 0, st, nbk, tau + b0, Gt, T);
         APW_TRY(gemm_cn(0, nbk, nw, n, Vb, n, coef, ldc, S, nbk, 1.0, 0.0, part, 0, st));
         const int64_t tot = (int64_t)nw * nbk;
         hipLaunchKernelGGL(k_wy_ts, dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, nbk, nw, T, S, Sp);
