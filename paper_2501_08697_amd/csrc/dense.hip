@@ -37,28 +37,7 @@ constexpr double kClusterTol = 1e-7;   // relative eigenvalue gap below which ve
 __device__ __forceinline__ z64 zconj(z64 a) { return z64{a.re, -a.im}; }
 __device__ __forceinline__ double zabs2(z64 a) { return a.re * a.re + a.im * a.im; }
 
-// Block-wide sum of one double per thread (fixed order: deterministic).
-__device__ double block_sum(double v, double *red) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    __syncthreads();
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int i = 0; i < nw; ++i) s += red[i];
-    __syncthreads();
-    return s;
-}
-
 // --------------------------------------------------------------- Cholesky --
-// Wave-wide sum (fixed butterfly order).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // G (n x n, ld) Hermitian positive definite; its lower triangle is replaced
 // by L with G = L L^H (right-looking, in global memory, one work-group).
 // info = 0, or k + 1 when the k-th pivot is not positive.
@@ -192,10 +171,10 @@ __global__ __launch_bounds__(256) void k_trinv(int n, const z64 *__restrict__ L,
 constexpr int kPanel = 8;   // columns per panel of the blocked reduction
 constexpr int kRows = 64;   // rows per LDS chunk of the trailing update
 // Orders from here on take one launch per column over many compute units (trd_multi): the
-// launches cost 8 us a column whatever the order, one compute unit's pass over the trailing
-// matrix grows with it. Measured, one compute unit / many: n = 64 356 / 495 us, 128 857 / 1013,
-// 192 1695 / 1587, 256 2956 / 2161.
-constexpr int kTrdMulti = 176;
+// launches cost 5 us a column whatever the order, one compute unit's pass over the trailing
+// matrix grows with it. Measured, one compute unit / many: n = 32 148 / 159 us, 64 313 / 334,
+// 80 416 / 420, 96 533 / 506, 128 782 / 696, 160 1143 / 879.
+constexpr int kTrdMulti = 88;
 constexpr int kSymvBatch = 8;    // loads in flight per thread in the symmetric product
 
 // A (n x n, ld) Hermitian, full storage. On exit d[n], e[n-1] hold T and

@@ -6,18 +6,18 @@
 // updates run on the MFMA GEMMs.
 //
 // Tridiagonal reduction T = Q^H A Q (LAPACK's blocked scheme, restated): columns
-// are reduced in panels of PL. One launch per column k = k0 + c (k_trd_step): every
+// are reduced in panels of kTrdPanel. One launch per column k = k0 + c (k_trd_step): every
 // work-group finishes the previous column's w vector (w = y - tau/2 (y^H v) v), forms
 // column k as stored minus the panel's rank-2 updates so far (A - V W^H - W V^H), its
 // Householder reflector H = I - tau v v^H (v[k+1] = 1, real off-diagonal beta) and the dot
-// products W^H v, V^H v, all of which is O(n PL) and done alike in each; then it computes
+// products W^H v, V^H v, all of which is O(n kTrdPanel) and done alike in each; then it computes
 // its own rows of y = tau (A22 v - V (W^H v) - W (V^H v)), A22 the trailing matrix as it
-// was when the panel started. The matrix rows are fetched at the start, behind the vector
-// work. After the panel the trailing matrix takes its updates at once (k_trd_update).
-// What bounds it is the chain of launches, each waiting on the one before: a column took
-// 11.5 us at n = 256 in one work-group and 20.1 us at n = 1024 in two launches (one
-// work-group for the vectors, then the product), 8.3 and 12.7 us now. The panel's rows staged in
-// LDS at the start measured the same (8.3 and 12.7); panels of 16 spill.
+// was when the panel started. After the panel the trailing matrix takes its updates at once
+// (k_trd_update). What bounds it is the chain of launches and, in a launch, of waits: 5.0 us at
+// n = 256 when each launch waits for memory once and sums by wave_sum, 7.8 with the panel read
+// where it was used and shuffled sums. A column took 11.5 us at n = 256 in one work-group and
+// 20.1 us at n = 1024 in two launches (one work-group for the vectors, then the product), 5.6
+// and 9.3 us now.
 //
 // Back-transformation coef = Q Z (Z the real tridiagonal eigenvectors): the
 // reflectors, kept as rows of Vr, are applied in blocks of kPL from the last to
@@ -43,12 +43,6 @@ constexpr int kCB = 64;       // columns per block of the blocked Cholesky
 __device__ __forceinline__ z64 zc(z64 a) { return z64{a.re, -a.im}; }
 __device__ __forceinline__ double za2(z64 a) { return a.re * a.re + a.im * a.im; }
 
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 struct TrdArgs {
     int n, ld;
     z64 *A;
@@ -61,7 +55,7 @@ struct TrdArgs {
 
 // Sum over the work-group of one complex value per thread (fixed order); one barrier.
 template <int NT> __device__ __forceinline__ z64 zsum(z64 v, z64 *red) {
-    const double re = wsum(v.re), im = wsum(v.im);
+    const double re = wave_sum(v.re), im = wave_sum(v.im);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = z64{re, im};
     __syncthreads();
     z64 s = z64{0.0, 0.0};
@@ -70,109 +64,149 @@ template <int NT> __device__ __forceinline__ z64 zsum(z64 v, z64 *red) {
     return s;
 }
 
+constexpr int kTrdPanel = 8;   // columns per panel
 constexpr int kTrdRows = 2;    // rows of y per wavefront
 constexpr int kTrdAhead = 4;   // 64-column pieces of a row fetched ahead
 
-template <int NT, int PL>
-__global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0, int c) {
+// Column k = k0 + C. ONE: a thread per row (m <= NT); its panel row comes in registers with the
+// first loads of the launch and goes to LDS for the dot products, so the launch waits for memory
+// once. Without it (the panel's 18 m values exceed LDS above m = 512) the panel is read from
+// memory where it is used. C is a template argument so that no load of an absent column is made.
+template <int NT, bool ONE, int C>
+__global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0) {
+    constexpr int PL = kTrdPanel, NW = NT / 64, L = C > 0 ? C - 1 : 0;   // L: the last column so far
     extern __shared__ __align__(16) unsigned char smem_trd[];
-    const int n = a.n, k = k0 + c, m = n - k;
+    const int n = a.n, k = k0 + C, m = n - k;
     z64 *xs = reinterpret_cast<z64 *>(smem_trd);   // [m] column k, rows k ..
-    z64 *wl = xs + m;                              // [m] w of panel column c - 1, rows k ..
+    z64 *wl = xs + m;                              // [m] w of panel column L, rows k ..
+    z64 *pv = wl + m, *pw = pv + C * m;            // ONE: V [C][m] and W [C - 1][m], rows k ..
     __shared__ z64 pk[2 * PL];                     // row k of V and W
     __shared__ z64 dots[2 * PL];                   // W^H x, V^H x over rows k + 2 ..
-    __shared__ z64 zred[NT / 64];
-    __shared__ double red[NT / 64];
+    __shared__ z64 zred[NW];
+    __shared__ double red[NW];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const z64 *V = a.P, *W = a.P + (int64_t)PL * n;
-    // this wavefront's rows of A22 and their panel rows
-    const int r0 = k + 1 + (blockIdx.x * (NT / 64) + wv) * kTrdRows;
-    z64 ar[kTrdRows][kTrdAhead], a0[kTrdRows], vr[kTrdRows], wr[kTrdRows];
-    const int lq = min(lane, max(c - 1, 0));
+    const z64 *V = a.P + k, *W = V + (int64_t)PL * n;   // rows k ..
+    const z64 *yp = a.y + (int64_t)((k - 1) & 1) * n + k;
+    // everything that can be asked for at once: this thread's row of the panel and of column k,
+    // row k of the panel, this wavefront's rows of A22
+    const int ic = min(tid, m - 1);
+    z64 vi[C > 0 ? C : 1], wi[C > 0 ? C : 1], x0, y0, yk, t0;
+    if constexpr (ONE) {
+        x0 = a.A[(int64_t)k * a.ld + k + ic];
+#pragma unroll
+        for (int q = 0; q < C; ++q) vi[q] = V[(int64_t)q * n + ic];
+#pragma unroll
+        for (int q = 0; q < L; ++q) wi[q] = W[(int64_t)q * n + ic];
+    }
+    if constexpr (C > 0) {
+        y0 = yp[ic];
+        yk = yp[0];
+        t0 = a.tau[k - 1];
+    }
+    const z64 pk0 = a.P[(int64_t)(tid % (2 * PL)) * n + k];
+    const int r0 = k + 1 + (blockIdx.x * NW + wv) * kTrdRows;
+    z64 ar[kTrdRows][kTrdAhead], a0[kTrdRows];
 #pragma unroll
     for (int r = 0; r < kTrdRows; ++r) {
-        const int i = min(r0 + r, n - 1);
-        const z64 *row = a.A + (int64_t)i * a.ld;
+        const z64 *row = a.A + (int64_t)min(r0 + r, n - 1) * a.ld;
 #pragma unroll
         for (int u = 0; u < kTrdAhead; ++u) ar[r][u] = row[min(k + 2 + lane + 64 * u, n - 1)];
         a0[r] = row[k + 1];
-        vr[r] = V[(int64_t)lq * n + i];
-        wr[r] = W[(int64_t)lq * n + i];
     }
-    if (tid < 2 * PL && tid % PL < c) pk[tid] = a.P[(int64_t)tid * n + k];
-    // w of column c - 1 over rows k .. (row k = its reflector's leading 1)
+    if (tid < 2 * PL) pk[tid] = pk0;   // columns from C on are never read
+    // w of column L over rows k .. (row k = its reflector's leading 1)
     z64 wk = z64{0.0, 0.0};   // w at row k
-    if (c > 0) {
-        const z64 *yp = a.y + (int64_t)((k - 1) & 1) * n, *vp = V + (int64_t)(c - 1) * n;
+    z64 al = z64{0.0, 0.0};
+    if constexpr (C > 0) {
         z64 s = z64{0.0, 0.0};
-        for (int i = tid; i < m; i += NT) {
-            const z64 yv = yp[k + i], v = vp[k + i];
-            wl[i] = yv;
-            xs[i] = v;
-            s = s + cmulc(v, yv);   // conj(y) v
+        if constexpr (ONE) {
+            if (tid < m) s = cmulc(vi[L], y0);   // conj(y) v
+        } else {
+            for (int i = tid; i < m; i += NT) {
+                const z64 yv = yp[i], v = V[(int64_t)L * n + i];
+                wl[i] = yv;
+                xs[i] = v;
+                s = s + cmulc(v, yv);
+            }
         }
-        const z64 yk = yp[k], t = a.tau[k - 1];
         s = zsum<NT>(s, zred);
-        const z64 al = cmul(z64{-0.5 * t.re, -0.5 * t.im}, s);
-        for (int i = tid; i < m; i += NT) {
-            const z64 w = wl[i] + cmul(al, xs[i]);
-            wl[i] = w;
-            if (blockIdx.x == 0) a.P[(int64_t)(PL + c - 1) * n + k + i] = w;
-        }
+        al = cmul(z64{-0.5 * t0.re, -0.5 * t0.im}, s);
         wk = yk + al;
+    } else {
+        __syncthreads();
     }
-    // column k, rows k ..: conj(row k of A) minus the panel's updates of columns q < c.
-    // The panel values are loaded before any is used (clamped to column c - 1, whose W
-    // comes from wl: this launch is writing it).
+    // column k, rows k ..: conj(row k of A) minus the panel's updates of columns q < C
     double p = 0.0;
     for (int i = tid; i < m; i += NT) {
-        z64 x = zc(a.A[(int64_t)k * a.ld + k + i]);
-        if (c > 0) {
-            z64 vi[PL], wi[PL];
+        if constexpr (!ONE) {
+            x0 = a.A[(int64_t)k * a.ld + k + i];
 #pragma unroll
-            for (int q = 0; q < PL; ++q) {
-                vi[q] = V[(int64_t)min(q, c - 1) * n + k + i];
-                wi[q] = W[(int64_t)max(min(q, c - 2), 0) * n + k + i];
-            }
+            for (int q = 0; q < C; ++q) vi[q] = V[(int64_t)q * n + i];
 #pragma unroll
-            for (int q = 0; q < PL; ++q)
-                if (q < c) {
-                    const z64 w = q == c - 1 ? wl[i] : wi[q];
-                    const z64 wq = q == c - 1 ? wk : pk[PL + q];
-                    x = x - cmulc(vi[q], wq) - cmulc(w, pk[q]);   // v_i conj(w_k) + w_i conj(v_k)
-                }
+            for (int q = 0; q < L; ++q) wi[q] = W[(int64_t)q * n + i];
+            if constexpr (C > 0) y0 = wl[i];
         }
+        z64 x = zc(x0);
+        if constexpr (C > 0) {
+            wi[L] = y0 + cmul(al, vi[L]);
+            wl[i] = wi[L];
+            if (blockIdx.x == 0) a.P[(int64_t)(PL + L) * n + k + i] = wi[L];
+        }
+#pragma unroll
+        for (int q = 0; q < C; ++q)   // v_i conj(w_k) + w_i conj(v_k)
+            x = x - cmulc(vi[q], q == L ? wk : pk[PL + q]) - cmulc(wi[q], pk[q]);
         xs[i] = x;
+        if constexpr (ONE) {
+#pragma unroll
+            for (int q = 0; q < C; ++q) pv[q * m + i] = vi[q];
+#pragma unroll
+            for (int q = 0; q < L; ++q) pw[q * m + i] = wi[q];
+        }
         if (i >= 2) p += za2(x);
     }
-    p = wsum(p);
+    p = wave_sum(p);
     if (lane == 0) red[wv] = p;
     __syncthreads();
-    // W^H x and V^H x over rows k + 2 .., one wavefront per product
-    for (int q2 = wv; q2 < 2 * c; q2 += NT / 64) {
-        const bool isw = q2 < c;
-        const int q = isw ? q2 : q2 - c;
-        const bool from_wl = isw && q == c - 1;
-        const z64 *col = (isw ? W : V) + (int64_t)q * n + k;
-        z64 s = z64{0.0, 0.0};
-        for (int i = 2 + lane; i < m; i += 256) {   // four rows per lane in flight
-            z64 u[4];
+    auto vat = [&](int q, int i) { return ONE ? pv[q * m + i] : V[(int64_t)q * n + i]; };   // rows from k
+    auto wat = [&](int q, int i) { return q == L ? wl[i] : ONE ? pw[q * m + i] : W[(int64_t)q * n + i]; };
+    // W^H x and V^H x over rows k + 2 ..; a wavefront takes its products together
+    if constexpr (C > 0) {
+        constexpr int ND = (2 * C + NW - 1) / NW;
+        z64 s[ND];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int ii = min(i + 64 * r, m - 1);
-                u[r] = from_wl ? wl[ii] : col[ii];
+        for (int u = 0; u < ND; ++u) s[u] = z64{0.0, 0.0};
+        for (int i = 2 + lane; i < m; i += 64) {
+            const z64 x = xs[i];
+#pragma unroll
+            for (int u = 0; u < ND; ++u) {
+                const int q = min(wv + NW * u, 2 * C - 1);
+                s[u] = s[u] + cmulc(x, q < C ? wat(q, i) : vat(q - C, i));   // conj(u) x
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (i + 64 * r < m) s = s + cmulc(xs[i + 64 * r], u[r]);   // conj(u) x
         }
-        const double sr = wsum(s.re), si = wsum(s.im);
-        if (lane == 0) dots[(isw ? 0 : PL) + q] = z64{sr, si};
+#pragma unroll
+        for (int u = 0; u < ND; ++u) {
+            const int q = wv + NW * u;
+            const double sr = wave_sum(s[u].re), si = wave_sum(s[u].im);
+            if (lane == 0 && q < 2 * C) dots[q < C ? q : PL + q - C] = z64{sr, si};
+        }
+    }
+    // W and V at row k + 1 and at this wavefront's rows, lane q < C the column q
+    const int lq = min(lane, L);
+    z64 w1 = z64{0.0, 0.0}, v1 = w1, vr[kTrdRows], wr[kTrdRows];
+    if constexpr (C > 0) {
+        w1 = wat(lq, 1);
+        v1 = vat(lq, 1);
+#pragma unroll
+        for (int r = 0; r < kTrdRows; ++r) {
+            const int i = min(r0 + r, n - 1) - k;
+            vr[r] = vat(lq, i);
+            wr[r] = wat(lq, i);
+        }
     }
     __syncthreads();
     double xn2 = 0.0;
 #pragma unroll
-    for (int q = 0; q < NT / 64; ++q) xn2 += red[q];
+    for (int q = 0; q < NW; ++q) xn2 += red[q];
     const z64 alpha = xs[1];
     double beta = alpha.re;
     z64 t = z64{0.0, 0.0}, scale = z64{0.0, 0.0};
@@ -182,6 +216,45 @@ __global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0, int c) {
         const z64 den = z64{alpha.re - beta, alpha.im};   // scale = 1 / (alpha - beta)
         const double dd = za2(den);
         scale = z64{den.re / dd, -den.im / dd};
+    }
+    // y = tau (A22 v - V (W^H v) - W (V^H v)) for the wavefront's rows, v = [1, scale x];
+    // lane q < C takes the panel column q of the correction
+    z64 wd = z64{0.0, 0.0}, vd = wd;   // W_q^H v, V_q^H v
+    if (C > 0 && lane < C) {
+        wd = zc(w1) + cmul(scale, dots[lane]);
+        vd = zc(v1) + cmul(scale, dots[PL + lane]);
+    }
+    z64 s[kTrdRows];
+#pragma unroll
+    for (int r = 0; r < kTrdRows; ++r) s[r] = z64{0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < kTrdAhead; ++u) {
+        const int j = 2 + lane + 64 * u;
+        const z64 x = j < m ? xs[j] : z64{0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < kTrdRows; ++r) s[r] = s[r] + (j < m ? cmul(ar[r][u], x) : z64{0.0, 0.0});
+    }
+    for (int j = 2 + lane + 64 * kTrdAhead; j < m; j += 256) {
+        z64 v[kTrdRows][4];
+#pragma unroll
+        for (int r = 0; r < kTrdRows; ++r)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                v[r][u] = a.A[(int64_t)min(r0 + r, n - 1) * a.ld + k + min(j + 64 * u, m - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j + 64 * u < m) {
+                const z64 x = xs[j + 64 * u];
+#pragma unroll
+                for (int r = 0; r < kTrdRows; ++r) s[r] = s[r] + cmul(v[r][u], x);
+            }
+    }
+#pragma unroll
+    for (int r = 0; r < kTrdRows; ++r) {
+        s[r] = cmul(scale, s[r]);
+        if (C > 0 && lane < C) s[r] = s[r] - cmul(vr[r], wd) - cmul(wr[r], vd);
+        const double sr = wave_sum(s[r].re), si = wave_sum(s[r].im);
+        if (lane == 0 && r0 + r < n) a.y[(int64_t)(k & 1) * n + r0 + r] = cmul(t, a0[r] + z64{sr, si});
     }
     if (blockIdx.x == 0) {
         if (tid == 0) {
@@ -194,40 +267,8 @@ __global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0, int c) {
             if (i == k + 1) v = z64{1.0, 0.0};
             else if (i > k + 1) v = cmul(xs[i - k], scale);
             a.Vr[(int64_t)k * n + i] = v;
-            if (i > k) a.P[(int64_t)c * n + i] = v;
+            if (i > k) a.P[(int64_t)C * n + i] = v;
         }
-    }
-    // y = tau (A22 v - V (W^H v) - W (V^H v)) for the wavefront's rows, v = [1, scale x];
-    // lane q < c takes the panel column q of the correction
-    z64 wd = z64{0.0, 0.0}, vd = z64{0.0, 0.0};   // W_q^H v, V_q^H v
-    if (lane < c) {
-        const z64 w1 = lane == c - 1 ? wl[1] : W[(int64_t)lane * n + k + 1];
-        wd = zc(w1) + cmul(scale, dots[lane]);
-        vd = zc(V[(int64_t)lane * n + k + 1]) + cmul(scale, dots[PL + lane]);
-    }
-#pragma unroll
-    for (int r = 0; r < kTrdRows; ++r) {
-        const int i = r0 + r;
-        if (i >= n) break;
-        const z64 *row = a.A + (int64_t)i * a.ld + k;
-        z64 s = z64{0.0, 0.0};
-#pragma unroll
-        for (int u = 0; u < kTrdAhead; ++u) {
-            const int j = 2 + lane + 64 * u;
-            if (j < m) s = s + cmul(ar[r][u], xs[j]);
-        }
-        for (int j = 2 + lane + 64 * kTrdAhead; j < m; j += 256) {
-            z64 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = row[min(j + 64 * u, m - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (j + 64 * u < m) s = s + cmul(v[u], xs[j + 64 * u]);
-        }
-        s = cmul(scale, s);
-        if (lane < c) s = s - cmul(vr[r], wd) - cmul(lane == c - 1 ? wl[i - k] : wr[r], vd);
-        const double sr = wsum(s.re), si = wsum(s.im);
-        if (lane == 0) a.y[(int64_t)(k & 1) * n + i] = cmul(t, a0[r] + z64{sr, si});
     }
 }
 
@@ -235,8 +276,8 @@ __global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0, int c) {
 // for i, j >= t0 = k0 + bw (full storage; entries (i, j) and (j, i) come out exactly conjugate).
 // The last w of the panel is finished here, by every work-group for its own rows and columns.
 // A work-group takes 32 rows x 64 columns; a thread one column and eight rows.
-template <int PL>
 __global__ __launch_bounds__(256) void k_trd_update(TrdArgs a, int k0, int bw) {
+    constexpr int PL = kTrdPanel;
     __shared__ z64 rv[PL][32], rw[PL][32];
     __shared__ z64 zred[4];
     const int n = a.n, t0 = k0 + bw, kp = t0 - 1, tid = threadIdx.x;
@@ -389,31 +430,39 @@ __global__ __launch_bounds__(1024) void k_chol_diag(z64 *G, int ld, int j0, int 
 
 // ------------------------------------------------------------------ drivers --
 
-constexpr int kTrdPanel = 8;
-template <int NT, int PL> static int trd_panel_step(const TrdArgs &a, int k0, int c, hipStream_t st) {
+template <int NT, bool ONE, int C> static int trd_step(const TrdArgs &a, int k0, hipStream_t st) {
     static bool once = false;
     if (!once) {
-        APW_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_trd_step<NT, PL>),
+        APW_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_trd_step<NT, ONE, C>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024));
         once = true;
     }
-    const int m = a.n - k0 - c;
-    hipLaunchKernelGGL((k_trd_step<NT, PL>), dim3((unsigned)ceil_div(m - 1, NT / 64 * kTrdRows)), dim3(NT),
-                       2 * sizeof(z64) * (size_t)m, st, a, k0, c);
+    const int m = a.n - k0 - C;
+    const size_t lds = sizeof(z64) * (size_t)m * (ONE ? 2 + std::max(0, 2 * C - 1) : 2);
+    hipLaunchKernelGGL((k_trd_step<NT, ONE, C>), dim3((unsigned)ceil_div(m - 1, NT / 64 * kTrdRows)), dim3(NT), lds, st,
+                       a, k0);
     return ABACUS_PW_OK;
 }
 
-template <int PL> static int trd_reduce(const TrdArgs &a, hipStream_t st) {
-    for (int k0 = 0; k0 < a.n - 1; k0 += PL) {
-        const int bw = std::min(PL, a.n - 1 - k0);
-        for (int c = 0; c < bw; ++c) {
-            // a thread per element of the vectors, up to 512: 1024 leave 128 registers and spill
-            if (a.n - k0 - c <= 256) APW_TRY((trd_panel_step<256, PL>(a, k0, c, st)));
-            else APW_TRY((trd_panel_step<512, PL>(a, k0, c, st)));
-        }
-        const int mt = a.n - k0 - bw;
-        hipLaunchKernelGGL((k_trd_update<PL>), dim3((unsigned)ceil_div(mt, 64), (unsigned)ceil_div(mt, 32)), dim3(256),
-                           0, st, a, k0, bw);
+// Columns k0 + C .. of a panel of bw
+template <int C> static int trd_panel(const TrdArgs &a, int k0, int bw, hipStream_t st) {
+    if constexpr (C < kTrdPanel) {
+        if (C >= bw) return ABACUS_PW_OK;
+        const int m = a.n - k0 - C;
+        if (m <= 256) APW_TRY((trd_step<256, true, C>(a, k0, st)));
+        else if (m <= 512) APW_TRY((trd_step<512, true, C>(a, k0, st)));
+        else APW_TRY((trd_step<512, false, C>(a, k0, st)));   // 1024 threads leave 128 registers and spill
+        return trd_panel<C + 1>(a, k0, bw, st);
+    }
+    return ABACUS_PW_OK;
+}
+
+static int trd_reduce(const TrdArgs &a, hipStream_t st) {
+    for (int k0 = 0; k0 < a.n - 1; k0 += kTrdPanel) {
+        const int bw = std::min(kTrdPanel, a.n - 1 - k0), mt = a.n - k0 - bw;
+        APW_TRY(trd_panel<0>(a, k0, bw, st));
+        hipLaunchKernelGGL(k_trd_update, dim3((unsigned)ceil_div(mt, 64), (unsigned)ceil_div(mt, 32)), dim3(256), 0, st,
+                           a, k0, bw);
         APW_TRY(check_launch("hetrd panel"));
     }
     return ABACUS_PW_OK;
@@ -424,7 +473,7 @@ size_t trd_scratch_elems(int n) { return (size_t)(2 * kTrdPanel + 2) * n; }   //
 // A -> d[n], e[n - 1], tau[n], Vr [n][n]; work: trd_scratch_elems(n) complex128. A is destroyed.
 int trd_multi(int n, z64 *A, int ld, double *d, double *e, z64 *tau, z64 *Vr, z64 *work, hipStream_t st) {
     TrdArgs a{n, ld, A, d, e, tau, Vr, work, work + (size_t)2 * kTrdPanel * n};
-    APW_TRY(trd_reduce<kTrdPanel>(a, st));
+    APW_TRY(trd_reduce(a, st));
     hipLaunchKernelGGL(k_trd_last, dim3(1), dim3(64), 0, st, A, ld, n, d);
     return check_launch("hetrd last");
 }

@@ -1,6 +1,6 @@
 """Orders at the edges of the many-CU tridiagonal reduction (abacus_pw_eigh_lowest): the switch
-from one compute unit (176), one work-group more or less, panel remainders of 8, 256 / 512
-threads, rows beyond the pieces fetched ahead. Checked as in test_gpu_dense.py: eigenvalues
+from one compute unit (88), one work-group more or less, panel remainders of 8, 256 / 512
+threads, the panel in LDS (512) or in memory, rows beyond the pieces fetched ahead. Checked as in test_gpu_dense.py: eigenvalues
 against LAPACK to 1e-12 of ||A||, residuals to 1e-11, orthonormality to 1e-9.
 """
 import numpy as np
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("n", [1, 2, 175, 176, 177, 183, 184, 255, 256, 257, 258, 321, 513, 515, 1025])
+@pytest.mark.parametrize("n", [1, 2, 87, 88, 89, 95, 176, 177, 255, 256, 257, 258, 321, 512, 513, 515, 1025])
 @pytest.mark.parametrize("zero_block", [False, True])
 def test_orders_around_the_switches(n, zero_block):
     from paper_2501_08697_amd import binding
