@@ -102,11 +102,11 @@ int d2d(void *dst, const void *src, size_t bytes, hipStream_t st) {
 // pivot status goes to *info_dev (the caller reads it later). T is unchanged.
 int cholqr_pass_async(int m, int npw, const z64 *T, z64 *Y, Buffers &b, int *info_dev, hipStream_t st) {
     z64 *G = b.G.as<z64>(), *Linv = b.Linv.as<z64>();
-    APW_TRY(gemm_cn(0, m, m, npw, T, npw, T, npw, G, m, 1.0, 0.0, b.part.ptr, 0, st));
-    sub_flops("gemm_cn", m, m, npw);
+    APW_TRY(gemm_cn_herm(m, npw, T, npw, G, m, b.part.ptr, st));
+    sub_flops("gemm_cn", m, 0.5 * (m + 1), npw);
     APW_TRY(potrf_inv_s(m, G, m, Linv, m, info_dev, b.chol.ptr, st));
-    sub_flops("gemm_nn", m, npw, m);
-    return gemm_nn(0, m, npw, m, Linv, m, T, npw, Y, npw, 1.0, 0.0, st);
+    sub_flops("gemm_nn", m, npw, 0.5 * (m + 1));
+    return gemm_nn_tri(m, npw, Linv, m, T, npw, Y, npw, st);
 }
 
 // Orthonormalise the m rows of T (length npw) by `passes` Cholesky-QR passes;
@@ -115,8 +115,8 @@ int cholqr_pass_async(int m, int npw, const z64 *T, z64 *Y, Buffers &b, int *inf
 int cholqr_rows(int m, int npw, z64 *T, z64 *Y, Buffers &b, int passes, hipStream_t st) {
     z64 *G = b.G.as<z64>(), *Linv = b.Linv.as<z64>();
     for (int pass = 0; pass < passes; ++pass) {
-        APW_TRY(gemm_cn(0, m, m, npw, T, npw, T, npw, G, m, 1.0, 0.0, b.part.ptr, 0, st));
-        sub_flops("gemm_cn", m, m, npw);
+        APW_TRY(gemm_cn_herm(m, npw, T, npw, G, m, b.part.ptr, st));
+        sub_flops("gemm_cn", m, 0.5 * (m + 1), npw);
         APW_TRY(potrf_inv_s(m, G, m, Linv, m, b.info.as<int>(), b.chol.ptr, st));
         int info = 0;
         APW_TRY(d2h(&info, b.info.ptr, sizeof(int), st));
@@ -127,8 +127,8 @@ int cholqr_rows(int m, int npw, z64 *T, z64 *Y, Buffers &b, int passes, hipStrea
             double tr = 0.0;
             for (double x : nrm) tr += x;
             const double shift = 11.0 * ((double)m * npw + (double)m * (m + 1)) * 2.220446049250313e-16 * tr;
-            APW_TRY(gemm_cn(0, m, m, npw, T, npw, T, npw, G, m, 1.0, 0.0, b.part.ptr, 0, st));
-            sub_flops("gemm_cn", m, m, npw);
+            APW_TRY(gemm_cn_herm(m, npw, T, npw, G, m, b.part.ptr, st));
+            sub_flops("gemm_cn", m, 0.5 * (m + 1), npw);
             APW_TRY(dav_add_diag(m, G, m, shift, st));
             APW_TRY(potrf_inv_s(m, G, m, Linv, m, b.info.as<int>(), b.chol.ptr, st));
             APW_TRY(d2h(&info, b.info.ptr, sizeof(int), st));
@@ -136,8 +136,8 @@ int cholqr_rows(int m, int npw, z64 *T, z64 *Y, Buffers &b, int passes, hipStrea
             ++passes;   // a shifted pass is followed by one more plain pass
             if (passes > 4) passes = 4;
         }
-        APW_TRY(gemm_nn(0, m, npw, m, Linv, m, T, npw, Y, npw, 1.0, 0.0, st));
-        sub_flops("gemm_nn", m, npw, m);
+        APW_TRY(gemm_nn_tri(m, npw, Linv, m, T, npw, Y, npw, st));
+        sub_flops("gemm_nn", m, npw, 0.5 * (m + 1));
         APW_TRY(d2d(T, Y, sizeof(z64) * (size_t)m * npw, st));
     }
     return ABACUS_PW_OK;
@@ -153,8 +153,8 @@ int rayleigh_ritz(int n, int nb, int nmax, Buffers &b, z64 **out, hipStream_t st
         ProfScope ps("eigensolver");
         APW_TRY(heev_lowest(n, Hw, nmax, nb, b.theta.as<double>(), coef, nmax, b.heev.ptr, st));
     }
-    APW_TRY(gemm_cn(0, nb, nb, n, coef, nmax, coef, nmax, G, nb, 1.0, 0.0, b.part.ptr, 0, st));
-    sub_flops("gemm_cn", nb, nb, n);
+    APW_TRY(gemm_cn_herm(nb, n, coef, nmax, G, nb, b.part.ptr, st));
+    sub_flops("gemm_cn", nb, 0.5 * (nb + 1), n);
     APW_TRY(dav_lowdin(nb, G, st));
     APW_TRY(gemm_nn(0, nb, n, nb, G, nb, coef, nmax, Hw, nmax, 1.0, 0.0, st));
     sub_flops("gemm_nn", nb, n, nb);

@@ -60,6 +60,9 @@ constexpr int kGemmWaves = 2;
 // kept all 36 A tiles in flight and read 15.7x the operands).
 // One launch covers up to kMaxBatch products of one shape M x N (the k-points of a call, whose
 // K = npw differ): grid z counts their splits one after the other.
+// herm: A and B are the same rows, so the result is Hermitian; tiles with i0 > j0 are left out
+// and k_reduce fills them in from their mirror images (36 of 64 tiles at 512 x 512: the Gram
+// matrix of 512 bands of 115k plane waves takes 2.05 ms, whole it took 2.95).
 struct CnBatch {
     int n;
     int K[kMaxBatch], kchunk[kMaxBatch], z0[kMaxBatch + 1];   // z0[p]: first split of product p in grid z
@@ -67,7 +70,7 @@ struct CnBatch {
 };
 template <typename T, typename TS = T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_cn_part(int M, int N, CnBatch bt, const cx<TS> *__restrict__ A,
-                                                      const cx<TS> *__restrict__ B, cx<T> *__restrict__ part, int gm) {
+                                                      const cx<TS> *__restrict__ B, cx<T> *__restrict__ part, int gm, int herm) {
     __shared__ cx<T> As[TM][KP];
     __shared__ cx<T> Bs[TN][KP];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -78,6 +81,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     const int grp = t / (gm * nn), first = grp * gm, rows = min(gm, nm - first);
     const int r = t - grp * gm * nn;
     const int i0 = (first + r % rows) * TM, j0 = (r / rows) * TN;
+    if (herm && i0 > j0) return;
     int pb = 0;
     while (pb + 1 < bt.n && bz >= bt.z0[pb + 1]) ++pb;
     const int s = bz;   // the partial sums of the products follow each other
@@ -166,12 +170,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
 }
 
 // C[j][i] = alpha * sum_s part[s][j][i] + beta * C[j][i]   (fixed summation order)
+// herm (beta = 0): the tiles i0 > j0 hold nothing and become the conjugates of their mirror images.
 template <typename T, typename TC = T>
 __global__ void k_reduce(int M, int N, int nsplit, const cx<T> *__restrict__ part, cx<TC> *__restrict__ C, int64_t ldc,
-                         double alpha, double beta) {
+                         double alpha, double beta, int herm) {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)M * N) return;
     const int j = (int)(idx / M), i = (int)(idx - (int64_t)j * M);
+    if (herm && i / TM > j / TN) return;
     const int64_t ss = (int64_t)M * N;
     double r4[4] = {0.0, 0.0, 0.0, 0.0}, i4[4] = {0.0, 0.0, 0.0, 0.0};   // four independent chains
     int s = 0;
@@ -200,6 +206,7 @@ __global__ void k_reduce(int M, int N, int nsplit, const cx<T> *__restrict__ par
         im *= alpha;
     }
     *c = cx<TC>{(TC)re, (TC)im};
+    if (herm && i / TM < j / TN) C[(int64_t)i * ldc + j] = cx<TC>{(TC)re, (TC)-im};
 }
 
 // P[j][i] = sum_s part[s][j][i]; Q[j][i] = sum_t D_blk(i)[i - lo][t] P[j][lo + t]
@@ -276,14 +283,16 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, RedBatch r
 // TS is the type A and B are stored in; they are rounded to T while staged.
 // One launch covers up to kMaxBatch products of one M and K (the k-points of a call, whose G =
 // npw differ): grid y counts their column tiles one after the other.
+// tri: A is lower triangular (zeros stored above its diagonal), so a row tile stops at its own
+// last column (a 512 x 512 inverse factor on 512 bands of 115k plane waves: 2.2 ms, whole 3.0).
 struct NnBatch {
     int n;
     int G[kMaxBatch], y0[kMaxBatch + 1];   // y0[p]: first column tile of product p in grid y
     int64_t ldb[kMaxBatch], ldc[kMaxBatch], a[kMaxBatch], b[kMaxBatch], c[kMaxBatch];   // rows, element offsets
 };
 template <typename T, typename TC, typename TS = T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_nn(int M, int K, NnBatch bt, const cx<TS> *__restrict__ A, int64_t lda,
-                                                 const cx<TS> *__restrict__ B, cx<TC> *__restrict__ C, double alpha, double beta) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_nn(int M, int Kall, NnBatch bt, const cx<TS> *__restrict__ A, int64_t lda,
+                                                 const cx<TS> *__restrict__ B, cx<TC> *__restrict__ C, double alpha, double beta, int tri) {
     __shared__ cx<T> As[TM][KP];
     __shared__ cx<T> Bs[KT][TN + 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -292,6 +301,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     int pb = 0;
     while (pb + 1 < bt.n && by >= bt.y0[pb + 1]) ++pb;
     const int j0 = bx * TM, g0 = (by - bt.y0[pb]) * TN, G = bt.G[pb];
+    const int K = tri ? min(Kall, j0 + TM) : Kall;
     const int64_t ldb = bt.ldb[pb], ldc = bt.ldc[pb];
     A += bt.a[pb];
     B += bt.b[pb];
@@ -545,7 +555,7 @@ int gemm_batch_limit(int M, int N, int K, int elem_bytes, int chunk_hint) {
 
 template <typename T, typename TS = T>
 static int cn_part(int M, int N, const CnProduct *pr, int np, const void *A, const void *B, void *part,
-                   int chunk_hint, bool wide, RedBatch *rb, hipStream_t st) {
+                   int chunk_hint, bool wide, RedBatch *rb, hipStream_t st, int herm = 0) {
     CnBatch bt;
     bt.n = np;
     bt.z0[0] = 0;
@@ -566,22 +576,22 @@ static int cn_part(int M, int N, const CnProduct *pr, int np, const void *A, con
     const int gm = tiles <= 192 ? (int)grid.x : std::max(1, std::min((int)grid.x, 96 / (int)grid.y));
     KernelTimer kt("gemm_cn", st);
     hipLaunchKernelGGL((k_gemm_cn_part<T, TS>), grid, dim3(256), 0, st, M, N, bt, static_cast<const cx<TS> *>(A),
-                       static_cast<const cx<TS> *>(B), static_cast<cx<T> *>(part), gm);
+                       static_cast<const cx<TS> *>(B), static_cast<cx<T> *>(part), gm, herm);
     return check_launch("gemm_cn");
 }
 
 // T: arithmetic and partial sums; TS: storage of A, B and C.
 template <typename T, typename TS = T>
 static int gemm_cn_t(int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
-                     int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st) {
+                     int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st, int herm = 0) {
     if (M <= 0 || N <= 0) return ABACUS_PW_OK;
     RedBatch rb;
     const CnProduct pr{K, lda, ldb, 0, 0};
-    APW_TRY((cn_part<T, TS>(M, N, &pr, 1, A, B, part, chunk_hint, sizeof(T) < sizeof(TS), &rb, st)));
+    APW_TRY((cn_part<T, TS>(M, N, &pr, 1, A, B, part, chunk_hint, sizeof(T) < sizeof(TS), &rb, st, herm)));
     const int64_t tot = (int64_t)M * N;
     KernelTimer kt("gemm_reduce", st);
     hipLaunchKernelGGL((k_reduce<T, TS>), dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, M, N, rb.z0[1],
-                       static_cast<const cx<T> *>(part), static_cast<cx<TS> *>(C), ldc, alpha, beta);
+                       static_cast<const cx<T> *>(part), static_cast<cx<TS> *>(C), ldc, alpha, beta, herm);
     return check_launch("gemm_reduce");
 }
 
@@ -591,7 +601,7 @@ int reduce_parts_f32_to_f64(int M, int N, int nsplit, const void *part, void *C,
     const int64_t tot = (int64_t)M * N;
     KernelTimer kt("gemm_reduce", st);
     hipLaunchKernelGGL((k_reduce<float, double>), dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, M, N, nsplit,
-                       static_cast<const c32 *>(part), static_cast<z64 *>(C), ldc, alpha, beta);
+                       static_cast<const c32 *>(part), static_cast<z64 *>(C), ldc, alpha, beta, 0);
     return check_launch("gemm_reduce");
 }
 
@@ -604,6 +614,10 @@ int gemm_cn(int prec, int M, int N, int K, const void *A, int64_t lda, const voi
             int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st) {
     return prec == 0 ? gemm_cn_t<double>(M, N, K, A, lda, B, ldb, C, ldc, alpha, beta, part, chunk_hint, st)
                      : gemm_cn_t<float>(M, N, K, A, lda, B, ldb, C, ldc, alpha, beta, part, chunk_hint, st);
+}
+
+int gemm_cn_herm(int M, int K, const void *A, int64_t lda, void *C, int64_t ldc, void *part, hipStream_t st) {
+    return gemm_cn_t<double>(M, M, K, A, lda, A, lda, C, ldc, 1.0, 0.0, part, 0, st, 1);
 }
 
 template <typename T>
@@ -632,7 +646,7 @@ int proj_dapply(int prec, int M, int N, const CnProduct *pr, int np, const void 
 
 template <typename T, typename TC, typename TS = T>
 static int gemm_nn_batch_t(int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
-                           void *C, double alpha, double beta, hipStream_t st) {
+                           void *C, double alpha, double beta, hipStream_t st, int tri = 0) {
     if (M <= 0) return ABACUS_PW_OK;
     NnBatch bt;
     bt.n = np;
@@ -650,7 +664,7 @@ static int gemm_nn_batch_t(int M, int K, const NnProduct *pr, int np, const void
     dim3 grid(ceil_div(M, TM), bt.y0[np]);
     KernelTimer kt("gemm_nn", st);
     hipLaunchKernelGGL((k_gemm_nn<T, TC, TS>), grid, dim3(256), 0, st, M, K, bt, static_cast<const cx<TS> *>(A), lda,
-                       static_cast<const cx<TS> *>(B), static_cast<cx<TC> *>(C), alpha, beta);
+                       static_cast<const cx<TS> *>(B), static_cast<cx<TC> *>(C), alpha, beta, tri);
     return check_launch("gemm_nn");
 }
 
@@ -677,6 +691,13 @@ int gemm_nn(int prec, int M, int G, int K, const void *A, int64_t lda, const voi
             int64_t ldc, double alpha, double beta, hipStream_t st) {
     return prec == 0 ? gemm_nn_t<double, double>(M, G, K, A, lda, B, ldb, C, ldc, alpha, beta, st)
                      : gemm_nn_t<float, float>(M, G, K, A, lda, B, ldb, C, ldc, alpha, beta, st);
+}
+
+int gemm_nn_tri(int M, int G, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc,
+                hipStream_t st) {
+    if (M <= 0 || G <= 0) return ABACUS_PW_OK;
+    const NnProduct pr{G, ldb, ldc, 0, 0, 0};
+    return gemm_nn_batch_t<double, double>(M, M, &pr, 1, A, lda, B, C, 1.0, 0.0, st, 1);
 }
 
 int gemm_nn_f32_into_f64(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,

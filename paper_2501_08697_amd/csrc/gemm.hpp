@@ -12,6 +12,10 @@ size_t gemm_cn_part_bytes(int M, int N, int K, int elem_bytes, int chunk_hint);
 int gemm_cn(int prec, int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
             int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st);
 
+// C = A^H A (M x M, FP64): half of gemm_cn's products, the other triangle as conjugates. part:
+// gemm_cn_part_bytes(M, M, K, 16, 0).
+int gemm_cn_herm(int M, int K, const void *A, int64_t lda, void *C, int64_t ldc, void *part, hipStream_t st);
+
 // Products of one launch, one per k-point of a call: their inner (or outer) length and rows,
 // and where their operands start (elements from the launch's base pointers).
 constexpr int kGemmMaxBatch = 8;
@@ -47,6 +51,10 @@ int gemm_nn_batch(int prec, int M, int K, const NnProduct *pr, int np, const voi
 
 int gemm_nn(int prec, int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
             int64_t ldc, double alpha, double beta, hipStream_t st);
+
+// C = A B with A [M][lda] lower triangular (zeros stored above the diagonal), FP64.
+int gemm_nn_tri(int M, int G, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc,
+                hipStream_t st);
 
 // As gemm_nn on complex128 A, B and C with FP32 products: the operands are rounded to
 // complex64 as they are staged, C accumulates in FP64 (basis updates of the
