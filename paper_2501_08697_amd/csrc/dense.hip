@@ -26,6 +26,7 @@
 //   k_unmtr      y = Q z for every wanted eigenvector (one wavefront each).
 //
 // All matrices are row-major with a leading dimension.
+#include "chol_device.hpp"
 #include "common.hpp"
 #include "dense.hpp"
 
@@ -71,38 +72,25 @@ __global__ __launch_bounds__(kNT) void k_potrf(int n, z64 *G, int ld, int *info)
 }
 
 // The same factorisation with the packed lower triangle (row i at i (i+1) / 2)
-// resident in LDS, for n <= kCholLds; L is written back to G at the end.
+// resident in LDS, for n <= kCholLds, in panels of 16 columns (chol_device.hpp); L is written
+// back to G at the end.
 constexpr int kCholLds = 136;   // 136 * 137 / 2 complex128 = 148 KB of LDS
 __host__ __device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }
 
-__global__ __launch_bounds__(kNT) void k_potrf_lds(int n, z64 *G, int ld, int *info) {
+constexpr int kCholThreads = 512;   // 1024 leave 128 registers a thread, and a panel row spills
+__global__ __launch_bounds__(kCholThreads) void k_potrf_lds(int n, z64 *G, int ld, int *info) {
     extern __shared__ __align__(16) unsigned char smem[];
     z64 *Lp = reinterpret_cast<z64 *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    for (int i = wv; i < n; i += kNT / 64)
+    for (int i = wv; i < n; i += kCholThreads / 64)
         for (int j = lane; j <= i; j += 64) Lp[tri(i) + j] = G[(int64_t)i * ld + j];
     __syncthreads();
-    const int tx = tid & 31, ty = tid >> 5;
-    for (int k = 0; k < n; ++k) {
-        const double dkk = Lp[tri(k) + k].re;
-        if (!(dkk > 0.0) || !isfinite(dkk)) {
-            if (tid == 0) *info = k + 1;
-            return;
-        }
-        const double lkk = sqrt(dkk), inv = 1.0 / lkk;
-        for (int i = k + 1 + tid; i < n; i += kNT) {
-            z64 &g = Lp[tri(i) + k];
-            g = z64{g.re * inv, g.im * inv};
-        }
-        __syncthreads();
-        if (tid == 0) Lp[tri(k) + k] = z64{lkk, 0.0};
-        for (int i = k + 1 + ty; i < n; i += 32) {
-            const z64 a = Lp[tri(i) + k];
-            for (int j = k + 1 + tx; j <= i; j += 32) Lp[tri(i) + j] = Lp[tri(i) + j] - cmulc(a, Lp[tri(j) + k]);
-        }
-        __syncthreads();
+    const int bad = chol_lds([&](int i, int j) -> z64 & { return Lp[tri(i) + j]; }, n);
+    if (bad) {
+        if (tid == 0) *info = bad;
+        return;
     }
-    for (int i = wv; i < n; i += kNT / 64)
+    for (int i = wv; i < n; i += kCholThreads / 64)
         for (int j = lane; j <= i; j += 64) G[(int64_t)i * ld + j] = Lp[tri(i) + j];
     if (tid == 0) *info = 0;
 }
@@ -692,7 +680,7 @@ int potrf_inv(int n, z64 *G, int ld, z64 *Linv, int ldi, int *info_dev, void *sc
                                             (int)(sizeof(z64) * (size_t)tri(kCholLds))));
                 attr = true;
             }
-            hipLaunchKernelGGL(k_potrf_lds, dim3(1), dim3(kNT), lds, st, n, G, ld, info_dev);
+            hipLaunchKernelGGL(k_potrf_lds, dim3(1), dim3(kCholThreads), lds, st, n, G, ld, info_dev);
         } else {
             hipLaunchKernelGGL(k_potrf, dim3(1), dim3(kNT), 0, st, n, G, ld, info_dev);
         }

@@ -28,7 +28,9 @@
 // and inverted in LDS by one work-group, the panel below it is L21 = A21 L11^-H
 // (GEMM) and the trailing matrix takes A22 -= L21 L21^H (GEMM).
 #include <algorithm>
+#include <type_traits>
 
+#include "chol_device.hpp"
 #include "common.hpp"
 #include "dense.hpp"
 #include "gemm.hpp"
@@ -368,61 +370,68 @@ __global__ void k_wy_ts(int nbk, int nw, const z64 *T, const z64 *S, z64 *Sp) {
     Sp[t] = acc;
 }
 
-// Diagonal block of the blocked Cholesky: factor G[j0 .. j0+jb)^2 in LDS (lower), write L11
-// back and Li = L11^{-1} (jb x jb, row-major). Skipped when an earlier block failed.
-__global__ __launch_bounds__(1024) void k_chol_diag(z64 *G, int ld, int j0, int jb, z64 *Li, int *info) {
-    __shared__ z64 L[kCB][kCB + 1];
-    __shared__ z64 X[kCB][kCB + 1];
-    __shared__ int bad;
-    const int tid = threadIdx.x;
+// Diagonal block of the blocked Cholesky: factor G[j0 .. j0+jb)^2 in LDS (lower, chol_device.hpp),
+// write L11 back and Li = L11^{-1} (jb x jb, row-major). Skipped when an earlier block failed.
+// The inverse: the 16 x 16 diagonal blocks by forward substitution, a column per lane, then
+// twice X21 = -X22 (L21 X11) for neighbouring blocks of 16 and of 32 on the matrix cores.
+// 39 us at jb = 64; column by column, with one thread per column of the inverse, 132 us.
+__global__ __launch_bounds__(512) void k_chol_diag(z64 *G, int ld, int j0, int jb, z64 *Li, int *info) {
+    __shared__ z64 L[kCB][kCB + 1];   // identity past jb
+    __shared__ z64 X[kCB][kCB + 1];   // lower triangle; the products L21 X11 above it, cleared at the end
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if (j0 == 0 && tid == 0) *info = 0;
-    if (tid == 0) bad = 0;
-    __syncthreads();
     if (j0 > 0 && *info != 0) return;
-    for (int t = tid; t < jb * jb; t += blockDim.x) {
-        const int i = t / jb, j = t - i * jb;
-        L[i][j] = j <= i ? G[(int64_t)(j0 + i) * ld + j0 + j] : z64{0.0, 0.0};
+    for (int t = tid; t < kCB * kCB; t += blockDim.x) {
+        const int i = t / kCB, j = t - i * kCB;
+        L[i][j] = j <= i && i < jb ? G[(int64_t)(j0 + i) * ld + j0 + j] : z64{i == j ? 1.0 : 0.0, 0.0};
     }
     __syncthreads();
-    for (int k = 0; k < jb; ++k) {
-        const double dkk = L[k][k].re;
-        if (!(dkk > 0.0) || !isfinite(dkk)) {
-            if (tid == 0) {
-                *info = j0 + k + 1;
-                bad = 1;
-            }
-            __syncthreads();
-            return;
-        }
-        const double lkk = sqrt(dkk), inv = 1.0 / lkk;
-        __syncthreads();
-        if (tid > k && tid < jb) L[tid][k] = z64{L[tid][k].re * inv, L[tid][k].im * inv};
-        __syncthreads();
-        if (tid == 0) L[k][k] = z64{lkk, 0.0};
-        const int m = jb - k - 1;
-        for (int t = tid; t < m * m; t += blockDim.x) {
-            const int i = k + 1 + t / m, j = k + 1 + t % m;
-            if (j <= i) L[i][j] = L[i][j] - cmulc(L[i][k], L[j][k]);
-        }
-        __syncthreads();
+    const int bad = chol_lds([&](int i, int j) -> z64 & { return L[i][j]; }, jb);
+    if (bad) {
+        if (tid == 0) *info = j0 + bad;
+        return;
     }
-    // Li = L^{-1} by forward substitution, one thread per column
-    if (tid < jb) {
-        const int c = tid;
-        for (int i = 0; i < c; ++i) X[i][c] = z64{0.0, 0.0};
-        X[c][c] = z64{1.0 / L[c][c].re, 0.0};
-        for (int i = c + 1; i < jb; ++i) {
-            z64 s = z64{0.0, 0.0};
-            for (int q = c; q < i; ++q) s = s + cmul(L[i][q], X[q][c]);
-            const double r = 1.0 / L[i][i].re;
-            X[i][c] = z64{-s.re * r, -s.im * r};
+    if (wv < kCB / 16 && lane < 16) {
+        const int o = 16 * wv;
+        z64 x[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            z64 s = z64{i == lane ? 1.0 : 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < i; ++q) s = s - cmul(L[o + i][o + q], x[q]);
+            const double r = 1.0 / L[o + i][o + i].re;
+            x[i] = z64{s.re * r, s.im * r};
+            X[o + i][o + lane] = x[i];
         }
     }
     __syncthreads();
+    // blocks of 16: pair p = rows and columns [32 p, 32 p + 32), one wavefront each
+    auto merge = [&](auto half, int o, int ti, int tj, bool second) {
+        constexpr int H = decltype(half)::value;
+        const int a = o, b = o + H;   // first rows of the upper and lower block
+        if (!second)
+            tile_product<H / 4>([&](int i, int k) { return L[b + 16 * ti + i][a + k]; },
+                                [&](int k, int j) { return X[a + k][a + 16 * tj + j]; },
+                                [&](int i, int j, z64 v) { X[a + 16 * ti + i][b + 16 * tj + j] = v; });
+        else
+            tile_product<H / 4>([&](int i, int k) { return X[b + 16 * ti + i][b + k]; },
+                                [&](int k, int j) { return X[a + k][b + 16 * tj + j]; },
+                                [&](int i, int j, z64 v) { X[b + 16 * ti + i][a + 16 * tj + j] = z64{-v.re, -v.im}; });
+    };
+    for (int second = 0; second < 2; ++second) {
+        if (wv < 2) merge(std::integral_constant<int, 16>{}, 32 * wv, 0, 0, second);
+        __syncthreads();
+    }
+    if (tid < 512) X[32 * (tid >> 8) + ((tid >> 4) & 15)][32 * (tid >> 8) + 16 + (tid & 15)] = z64{0.0, 0.0};
+    __syncthreads();
+    for (int second = 0; second < 2; ++second) {
+        if (wv < 4) merge(std::integral_constant<int, 32>{}, 0, wv >> 1, wv & 1, second);
+        __syncthreads();
+    }
     for (int t = tid; t < jb * jb; t += blockDim.x) {
         const int i = t / jb, j = t - i * jb;
         if (j <= i) G[(int64_t)(j0 + i) * ld + j0 + j] = L[i][j];
-        Li[t] = X[i][j];
+        Li[t] = j <= i ? X[i][j] : z64{0.0, 0.0};
     }
 }
 
@@ -562,7 +571,7 @@ int potrf_large(int n, z64 *G, int ld, int *info_dev, void *scratch, hipStream_t
     KernelTimer kt("potrf_mc", st);
     for (int j0 = 0; j0 < n; j0 += kCB) {
         const int jb = std::min(kCB, n - j0), j1 = j0 + jb, m = n - j1;
-        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(1024), 0, st, G, ld, j0, jb, Li, info_dev);
+        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), 0, st, G, ld, j0, jb, Li, info_dev);
         APW_TRY(check_launch("chol diag"));
         if (m == 0) break;
         // L21 = A21 L11^{-H}: tmp[i][q] = sum_r conj(Li[q][r]) A21[i][r]
