@@ -102,8 +102,10 @@ int reduce_parts_f32_to_f64(int M, int N, int nsplit, const void *part, void *C,
 size_t gemm_cn_bf16_of_f64_bytes(int M, int N, int K);
 int gemm_cn_bf16_of_f64(int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                         int64_t ldc, void *scratch, hipStream_t st);
-// out[g][i] = in[i][g] (complex128 [rows][ldi], g < cols) as packed bf16, zero for rows <= i < ldo.
-int pack_bf16_transpose(int rows, int cols, const void *in, int64_t ldi, void *out, int64_t ldo, hipStream_t st);
+// out[i][g] and outT[g][i] = in[i][g] (complex128 [rows][ldi], g < cols) as packed bf16, zero for
+// cols <= g < ldo and rows <= i < ldt; ldo = bf16_ld(cols), ldt = bf16_ld(rows).
+int pack_bf16_both(int rows, int cols, const void *in, int64_t ldi, void *out, int64_t ldo, void *outT, int64_t ldt,
+                   hipStream_t st);
 // C[j][g] += sum_i A[j][i] B[i][g] for j < N, g < G, i < K: Apk packed bf16 A [N][lda], BTpk packed bf16
 // transposed B [G][ldbt], lda and ldbt = bf16_ld(K) with zero padding; C complex128 [N][ldc].
 int gemm_nn_bf16_into_f64(int N, int G, int K, const void *Apk, int64_t lda, const void *BTpk, int64_t ldbt, void *C,

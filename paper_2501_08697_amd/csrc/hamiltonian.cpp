@@ -55,18 +55,15 @@ int operator_copies(const abacus_pw_problem &p, Plan &P, bool need_v32, bool nee
         P.beta32_src = capturing ? nullptr : p.beta;
     }
     if (need_bf && P.nproj > 0 && !(stat && P.betabf_src == p.beta)) {
-        // per k a [nproj][bf16_ld(npw_k)] block of packed bf16 pairs, rows zero-padded
+        // per k a [nproj][bf16_ld(npw_k)] block of packed bf16 pairs and its transpose, a
+        // [npw_k][bf16_ld(nproj)] block with the projector index contiguous, rows zero-padded
+        const int ldq = bf16_ld(P.nproj);
         for (int k = 0; k < P.nk; ++k) {
             const int npw = P.npw[k];
-            APW_TRY(pack_bf16_rows(P.nproj, npw, static_cast<const z64 *>(p.beta) + (size_t)P.nproj * P.pw_off[k], 1,
-                                   npw, P.betabf.as<uint32_t>() + (size_t)P.nproj * bf16_offset(P, k), bf16_ld(npw),
-                                   st));
+            APW_TRY(pack_bf16_both(P.nproj, npw, static_cast<const z64 *>(p.beta) + (size_t)P.nproj * P.pw_off[k], npw,
+                                   P.betabf.as<uint32_t>() + (size_t)P.nproj * bf16_offset(P, k), bf16_ld(npw),
+                                   P.betabfT.as<uint32_t>() + (size_t)ldq * P.pw_off[k], ldq, st));
         }
-        // and per k the transposed [npw_k][bf16_ld(nproj)] block, projector index contiguous
-        const int ldq = bf16_ld(P.nproj);
-        for (int k = 0; k < P.nk; ++k)
-            APW_TRY(pack_bf16_transpose(P.nproj, P.npw[k], static_cast<const z64 *>(p.beta) + (size_t)P.nproj * P.pw_off[k],
-                                        P.npw[k], P.betabfT.as<uint32_t>() + (size_t)ldq * P.pw_off[k], ldq, st));
         P.betabf_src = capturing ? nullptr : p.beta;
     }
     return ABACUS_PW_OK;
