@@ -23,11 +23,16 @@ int apply_h_backward_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, 
     const int io = prec == ABACUS_PW_FP32 ? 1 : 0;
     const size_t ib = io == 0 ? 16 : 8;
     APW_TRY(local_supported(P, fp));
-    if (grad_psi) APW_TRY(apply_h_all(p, P, prec, nb, dy, grad_psi, st));
-    if (grad_d && P.nproj > 0) {
-        APW_TRY(operator_copies(p, P, false, fp == 1, st));
-        APW_TRY(P.proj.ensure((size_t)nb * P.nproj * ib));
-        APW_TRY(P.proj2.ensure((size_t)nb * P.nproj * ib));
+    // H dY projects dY on its way; grad_D reads those projections instead of projecting again
+    const bool need_d = grad_d && P.nproj > 0;
+    const size_t pk = (size_t)nb * P.nproj * ib;   // projections of one k-point
+    if (need_d) {
+        APW_TRY(P.proj.ensure(pk));
+        APW_TRY(P.proj2.ensure(pk * (grad_psi ? P.nk : 1)));
+    }
+    if (grad_psi) APW_TRY(apply_h_all(p, P, prec, nb, dy, grad_psi, st, nullptr, 0, need_d ? P.proj2.ptr : nullptr));
+    if (need_d) {
+        if (!grad_psi) APW_TRY(operator_copies(p, P, false, fp == 1, st));
         APW_TRY(P.gemm_part.ensure(gemm_cn_part_bytes(P.nproj, nb, P.max_npw, (int)ib, g_splitk_chunk)));
         for (int k = 0; k < P.nk; ++k) {
             const KTables &K = P.k[k];
@@ -35,11 +40,13 @@ int apply_h_backward_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, 
                                      : static_cast<const void *>(P.beta32.as<char>() + (size_t)P.nproj * K.pw_off * 8);
             const char *xk = static_cast<const char *>(psi) + (size_t)nb * K.pw_off * ib;
             const char *yk = static_cast<const char *>(dy) + (size_t)nb * K.pw_off * ib;
+            char *qk = P.proj2.as<char>() + (grad_psi ? pk * k : 0);
             APW_TRY(gemm_cn(fp, P.nproj, nb, K.npw, bk, K.npw, xk, K.npw, P.proj.ptr, P.nproj, 1.0, 0.0,
                             P.gemm_part.ptr, g_splitk_chunk, st));
-            APW_TRY(gemm_cn(fp, P.nproj, nb, K.npw, bk, K.npw, yk, K.npw, P.proj2.ptr, P.nproj, 1.0, 0.0,
-                            P.gemm_part.ptr, g_splitk_chunk, st));
-            APW_TRY(grad_d_accumulate(fp, nb, P.nproj, P.proj.ptr, P.proj2.ptr, P.proj_blk_lo, P.proj_blk_n,
+            if (!grad_psi)
+                APW_TRY(gemm_cn(fp, P.nproj, nb, K.npw, bk, K.npw, yk, K.npw, qk, P.nproj, 1.0, 0.0,
+                                P.gemm_part.ptr, g_splitk_chunk, st));
+            APW_TRY(grad_d_accumulate(fp, nb, P.nproj, P.proj.ptr, qk, P.proj_blk_lo, P.proj_blk_n,
                                       P.proj_blk_doff, grad_d, k == 0, st));
         }
     }

@@ -490,22 +490,35 @@ int force_contract(int M, int G, int nb, const void *W, const void *psi, const v
     return check_launch("force_contract");
 }
 
-// grad_d[blk(i)][i - lo][t] (+)= sum_n Re(Q[n][i] conj(P[n][lo + t])), one thread per projector i.
+// grad_d[blk(i)][i - lo][t] (+)= sum_n Re(Q[n][i] conj(P[n][lo + t])): 64 projectors i by
+// kGradDGroups groups of bands (n = g mod kGradDGroups), group sums added in order. Bound by the
+// latency of its loads: 512 projectors x 256 bands took 207 us with one thread per projector in
+// one chain over the bands, now 25.
+constexpr int kGradDGroups = 16;
 template <typename T>
-__global__ void k_grad_d(int nb, int M, const cx<T> *__restrict__ P, const cx<T> *__restrict__ Q,
-                         const int *__restrict__ blo, const int *__restrict__ bn, const int *__restrict__ bdoff,
-                         double *__restrict__ gd, int first) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    const int lo = blo[i], n = bn[i];
-    double *out = gd + bdoff[i] + (int64_t)(i - lo) * n;
-    for (int t = 0; t < n; ++t) {
+__global__ __launch_bounds__(64 * kGradDGroups) void k_grad_d(int nb, int M, const cx<T> *__restrict__ P,
+                                                              const cx<T> *__restrict__ Q, const int *__restrict__ blo,
+                                                              const int *__restrict__ bn, const int *__restrict__ bdoff,
+                                                              double *__restrict__ gd, int first) {
+    __shared__ double red[kGradDGroups][64];
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6, i = blockIdx.x * 64 + lane, ic = min(i, M - 1);
+    const int lo = blo[ic], n = bn[ic];
+    double *out = gd + bdoff[ic] + (int64_t)(ic - lo) * n;
+    for (int t = 0; __syncthreads_or(t < n); ++t) {
+        const int tc = lo + min(t, n - 1);
         double s = 0.0;
-        for (int b = 0; b < nb; ++b) {
-            const cx<T> q = Q[(int64_t)b * M + i], p = P[(int64_t)b * M + lo + t];
+#pragma unroll 4
+        for (int b = g; b < nb; b += kGradDGroups) {
+            const cx<T> q = Q[(int64_t)b * M + ic], p = P[(int64_t)b * M + tc];
             s += (double)q.re * (double)p.re + (double)q.im * (double)p.im;
         }
-        out[t] = first ? s : out[t] + s;
+        red[g][lane] = s;
+        __syncthreads();
+        if (g == 0 && i < M && t < n) {
+            double r = red[0][lane];
+            for (int u = 1; u < kGradDGroups; ++u) r += red[u][lane];
+            out[t] = first ? r : out[t] + r;
+        }
     }
 }
 
@@ -722,10 +735,10 @@ int grad_d_accumulate(int prec, int nb, int M, const void *P, const void *Q, con
                       const int *bdoff, double *gd, int first, hipStream_t st) {
     KernelTimer kt("grad_d", st);
     if (prec == 0)
-        hipLaunchKernelGGL(k_grad_d<double>, dim3(ceil_div(M, 64)), dim3(64), 0, st, nb, M,
+        hipLaunchKernelGGL(k_grad_d<double>, dim3(ceil_div(M, 64)), dim3(64 * kGradDGroups), 0, st, nb, M,
                            static_cast<const z64 *>(P), static_cast<const z64 *>(Q), blo, bn, bdoff, gd, first);
     else
-        hipLaunchKernelGGL(k_grad_d<float>, dim3(ceil_div(M, 64)), dim3(64), 0, st, nb, M,
+        hipLaunchKernelGGL(k_grad_d<float>, dim3(ceil_div(M, 64)), dim3(64 * kGradDGroups), 0, st, nb, M,
                            static_cast<const c32 *>(P), static_cast<const c32 *>(Q), blo, bn, bdoff, gd, first);
     return check_launch("grad_d");
 }

@@ -150,7 +150,7 @@ size_t hwork_total(const size_t sz[kHWorkParts]) {
 }
 
 int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec, int nb, const void *psi, void *hpsi,
-                  hipStream_t st, bool refresh_copies, void *ext_ws, size_t ext_bytes) {
+                  hipStream_t st, bool refresh_copies, void *ext_ws, size_t ext_bytes, void *proj) {
     const bool bf = prec == ABACUS_PW_MIXED_BF16;
     const int fft_prec = prec == ABACUS_PW_FP64 ? 0 : 1;
     const int io_prec = prec == ABACUS_PW_FP32 ? 1 : 0;
@@ -227,7 +227,7 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
             pr[i] = CnProduct{Ki.npw, Ki.npw, Ki.npw, o * P.nproj, o * nb};
         }
         APW_TRY(proj_dapply(gemm_prec, P.nproj, nb, pr, np, bk, xg, p.dmat, P.proj_blk_lo, P.proj_blk_n,
-                            P.proj_blk_doff, nullptr, qk_ptr, gemm_part, g_splitk_chunk, mixed, gs));
+                            P.proj_blk_doff, proj ? static_cast<char *>(proj) + qk * (k - k0) : nullptr, qk_ptr, gemm_part, g_splitk_chunk, mixed, gs));
     }
     // hpsi[b0 .. b0+bbt) += B_k Q_k[b0 .. b0+bbt) for every k-point
     auto add_bq = [&](int b0, int bbt, hipStream_t s) -> int {
@@ -276,8 +276,8 @@ int apply_h_k(const abacus_pw_problem &p, Plan &P, int k, int prec, int nb, cons
 }
 
 int apply_h_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, const void *psi, void *hpsi, hipStream_t st,
-                void *ws, size_t ws_bytes) {
-    return apply_h_range(p, P, 0, P.nk, prec, nb, psi, hpsi, st, true, ws, ws_bytes);
+                void *ws, size_t ws_bytes, void *proj) {
+    return apply_h_range(p, P, 0, P.nk, prec, nb, psi, hpsi, st, true, ws, ws_bytes, proj);
 }
 
 int apply_h_workspace(Plan &P, int prec, int nb, size_t *bytes) {

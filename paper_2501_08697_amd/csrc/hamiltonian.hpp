@@ -19,13 +19,14 @@ constexpr int kHWorkParts = 6;
 
 // hpsi = H psi for nb bands at the k-points [k0, k1) (psi starts at k0's block). The work
 // buffers come from the plan (grown as needed) unless ws (ws_bytes) is given, in which case
-// they are carved from it and nothing is allocated.
+// they are carved from it and nothing is allocated. proj (FP64 and FP32, may be NULL) also receives
+// the projections P_k = B_k^H psi_k, [k1 - k0][nb][nproj] in psi's type.
 int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec, int nb, const void *psi, void *hpsi,
-                  hipStream_t st, bool refresh_copies, void *ws = nullptr, size_t ws_bytes = 0);
+                  hipStream_t st, bool refresh_copies, void *ws = nullptr, size_t ws_bytes = 0, void *proj = nullptr);
 
 // hpsi = H psi for nb bands at every k-point (packed [k][nb][npw_k]).
 int apply_h_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, const void *psi, void *hpsi, hipStream_t st,
-                void *ws = nullptr, size_t ws_bytes = 0);
+                void *ws = nullptr, size_t ws_bytes = 0, void *proj = nullptr);
 
 // Bytes of caller work space apply_h_all needs for (prec, nb) with the current knobs; allocates
 // the plan's operator copies for prec (and the side stream when the overlap knob is on) so a
