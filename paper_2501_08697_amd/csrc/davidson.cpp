@@ -382,9 +382,7 @@ int davidson_k(const abacus_pw_problem &p, Plan &P, int k, int hprec, int nb, z6
             // not positive definite: Cholesky-QR with the shifted retry
             APW_TRY(cholqr_rows(m, npw, T, Y, b, 2, st));
         } else {
-            APW_TRY(d2d(T, Y, vb * m, st));
-            APW_TRY(cholqr_pass_async(m, npw, T, Y, b, b.info2.as<int>(), st));
-            APW_TRY(d2d(T, Y, vb * m, st));
+            APW_TRY(cholqr_pass_async(m, npw, Y, T, b, b.info2.as<int>(), st));
             check_info2 = true;
         }
         {

@@ -339,10 +339,15 @@ __global__ void k_real_rows(const double *Z, int ldz, int n, int nw, z64 *coef, 
 
 // T (upper triangular, nbk x nbk, row-major) of the compact WY form of H_0 ... H_{nbk-1}:
 // T[q][q] = tau_q, T[r][q] = -tau_q sum_{s = r}^{q-1} T[r][s] G[s][q] for r < q, where
-// G[s][q] = v_s^H v_q is given transposed: Gt[q * nbk + s] = G[s][q].
-__global__ void k_wy_t(int nbk, const z64 *tau, const z64 *Gt, z64 *T) {
+// G[s][q] = v_s^H v_q is given transposed: Gt[q * nbk + s] = G[s][q]. One work-group per block of
+// reflectors (kPL of the nref, the last one fewer): a block's serial recurrence takes 57 us, and
+// launched one by one between the products of the blocks it was 4.3 ms of a Davidson run at 120^3.
+__global__ void k_wy_t(int nref, const z64 *tau, const z64 *Gt, z64 *T) {
     __shared__ z64 Ts[kPL][kPL];
-    const int r = threadIdx.x;
+    const int r = threadIdx.x, b0 = blockIdx.x * kPL, nbk = min(kPL, nref - b0);
+    tau += b0;
+    Gt += (int64_t)b0 * kPL;
+    T += (int64_t)b0 * kPL;
     for (int q = 0; q < nbk; ++q) {
         if (r < q) {
             z64 acc = z64{0.0, 0.0};
@@ -495,7 +500,7 @@ size_t heev_large_scratch_bytes(int n, int nw) {
            + (size_t)n * n * zn                           // Vr
            + trd_scratch_elems(n) * zn                    // panel vectors, y
            + (size_t)n * n * sizeof(double)               // Z
-           + (size_t)2 * kPL * kPL * zn                   // Gram, T
+           + (size_t)2 * (n + kPL) * kPL * zn             // Gram, T of every block
            + (size_t)2 * nw * kPL * zn                    // S, S'
            + gemm_cn_part_bytes(kPL, nw, n, 16, 0) + 4096;
 }
@@ -520,8 +525,9 @@ int heev_lowest_large(int n, z64 *A, int ld, int nw, double *w, z64 *coef, int l
     z64 *Vr = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)n * n));
     z64 *trd = reinterpret_cast<z64 *>(take(sizeof(z64) * trd_scratch_elems(n)));
     double *Z = reinterpret_cast<double *>(take(sizeof(double) * (size_t)n * n));
-    z64 *Gt = reinterpret_cast<z64 *>(take(sizeof(z64) * kPL * kPL));
-    z64 *T = reinterpret_cast<z64 *>(take(sizeof(z64) * kPL * kPL));
+    const size_t tri_bytes = sizeof(z64) * (size_t)ceil_div(n, kPL) * kPL * kPL;
+    z64 *Gt = reinterpret_cast<z64 *>(take(tri_bytes));
+    z64 *T = reinterpret_cast<z64 *>(take(tri_bytes));
     z64 *S = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)nw * kPL));
     z64 *Sp = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)nw * kPL));
     void *part = take(gemm_cn_part_bytes(kPL, nw, n, 16, 0));
@@ -543,14 +549,19 @@ int heev_lowest_large(int n, z64 *A, int ld, int nw, double *w, z64 *coef, int l
     }
     // coef = H_0 ... H_{n-2} Z, blocks of kPL reflectors from the last block to the first
     const int nref = n - 1;
-    for (int b0 = ((nref - 1) / kPL) * kPL; b0 >= 0; b0 -= kPL) {
+    for (int b0 = 0; b0 < nref; b0 += kPL) {
         const int nbk = std::min(kPL, nref - b0);
         const z64 *Vb = Vr + (size_t)b0 * n;
-        APW_TRY(gemm_cn(0, nbk, nbk, n, Vb, n, Vb, n, Gt, nbk, 1.0, 0.0, part, 0, st));
-        hipLaunchKernelGGL(k_wy_t, dim3(1), dim3(kPL), 0, st, nbk, tau + b0, Gt, T);
+        APW_TRY(gemm_cn(0, nbk, nbk, n, Vb, n, Vb, n, Gt + (size_t)b0 * kPL, nbk, 1.0, 0.0, part, 0, st));
+    }
+    hipLaunchKernelGGL(k_wy_t, dim3(ceil_div(nref, kPL)), dim3(kPL), 0, st, nref, tau, Gt, T);
+    APW_TRY(check_launch("wy T"));
+    for (int b0 = ((nref - 1) / kPL) * kPL; b0 >= 0; b0 -= kPL) {
+        const int nbk = std::min(kPL, nref - b0);
+        const z64 *Vb = Vr + (size_t)b0 * n, *Tb = T + (size_t)b0 * kPL;
         APW_TRY(gemm_cn(0, nbk, nw, n, Vb, n, coef, ldc, S, nbk, 1.0, 0.0, part, 0, st));
         const int64_t tot = (int64_t)nw * nbk;
-        hipLaunchKernelGGL(k_wy_ts, dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, nbk, nw, T, S, Sp);
+        hipLaunchKernelGGL(k_wy_ts, dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, st, nbk, nw, Tb, S, Sp);
         APW_TRY(check_launch("wy"));
         APW_TRY(gemm_nn(0, nw, n, nbk, Sp, nbk, Vb, n, coef, ldc, -1.0, 1.0, st));
     }
