@@ -81,6 +81,7 @@ int density_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, const voi
     const int fp = prec == ABACUS_PW_FP64 ? 0 : 1;
     const int io = prec == ABACUS_PW_FP32 ? 1 : 0;
     APW_TRY(local_supported(P, fp));
+    if (local_density_columns(P, fp)) return local_density_by_columns(P, nb, psi, occ, rho, st);
     const int bb = default_band_batch(P, nb);
     APW_TRY(P.slab.ensure(local_slab_bytes(P, fp, P.nk * bb)));
     APW_TRY(P.gradv_part.ensure(sizeof(double) * (size_t)kGradVGroups * P.N));

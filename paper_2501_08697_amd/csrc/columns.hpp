@@ -591,6 +591,13 @@ PlaneShape plane_shape(const Plan &P);
 int columns_inverse(const ColumnsCall &c, const void *psi, const double *v);
 int columns_plane(const ColumnsCall &c);
 int columns_forward(const ColumnsCall &c, const void *psi, void *hpsi);
+// Band density of the batch's columns (columns_density.hip): whether the grid has a kernel, the
+// partial grids for nvb bands, the plane pass (adding w |psi|^2 of its bands to part [G][N3][N1][N2];
+// first: overwriting), and their sum. occ [nk][nb_total] from the call's first k-point.
+bool columns_density_fits(const Plan &P);
+int columns_density_groups(const Plan &P, int nvb);
+int columns_density(const ColumnsCall &c, const double *occ, double *part, int G, int first);
+int columns_density_sum(const Plan &P, const double *part, int G, double *rho, hipStream_t st);
 // columns_plane for the grids with x length N1 (instantiated in columns_plane_*.hip)
 template <int N1> int columns_plane_n1(const ColumnsCall &c);
 

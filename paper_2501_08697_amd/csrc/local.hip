@@ -1223,6 +1223,27 @@ int local_band_batch(const Plan &P, int fft_prec, int nkb, int nb) {
     return (int)std::max<size_t>(1, std::min<size_t>(nb, (size_t(4) << 30) / per));
 }
 
+// The density of every band and k-point (occ [nk][nb]) through the column passes, where use_columns
+// holds and the plane kernel exists: at 72^3 x 128 bands 40 us of z pass and 146 of plane pass (the
+// plane pass bound by its transforms, as k_plane), where the slab passes took 145 and 101.
+bool local_density_columns(const Plan &P, int fft_prec) {
+    return use_columns(P, fft_prec) && columns_density_fits(P);
+}
+
+int local_density_by_columns(Plan &P, int nb, const void *psi, const double *occ, double *rho, hipStream_t st) {
+    const int bb = local_band_batch(P, 0, P.nk, nb), G = columns_density_groups(P, P.nk * bb);
+    APW_TRY(P.slab.ensure(column_bytes(P, 0) * P.nk * bb));
+    APW_TRY(P.gradv_part.ensure(sizeof(double) * (size_t)G * P.N));
+    double *part = P.gradv_part.as<double>();
+    for (int b0 = 0; b0 < nb; b0 += bb) {
+        const BatchArgs ba{nb, 0, b0, std::min(bb, nb - b0)};
+        const ColumnsCall c{&P, 0, P.nk, ba, P.slab.ptr, nullptr, st};
+        APW_TRY(columns_inverse(c, psi, nullptr));
+        APW_TRY(columns_density(c, occ, part, G, b0 == 0));
+    }
+    return columns_density_sum(P, part, G, rho, st);
+}
+
 size_t local_work_bytes(const Plan &P, int fft_prec, int nkb, int nb) {
     const int nvb = nkb * local_band_batch(P, fft_prec, nkb, nb);
     if (!use_columns(P, fft_prec)) return local_slab_bytes(P, fft_prec, nvb);

@@ -40,6 +40,9 @@ int local_gradv_accumulate(const Plan &P, int fft_prec, const void *slab_x, cons
 // virtual band b = kk * bbt + j of the batch has w_b = occ[kk * nb + b0 + j].
 int local_density_accumulate(const Plan &P, int fft_prec, const void *slab, int nbands, const double *occ, int nb,
                              int b0, int bbt, double *part, int G, int first, hipStream_t st);
+// Band density of every k-point through the column passes, where local_density_columns holds.
+bool local_density_columns(const Plan &P, int fft_prec);
+int local_density_by_columns(Plan &P, int nb, const void *psi, const double *occ, double *rho, hipStream_t st);
 // out = scale * sum_g part[g]   (fixed order)
 int local_sum_parts(const Plan &P, const double *part, int G, double scale, double *out, hipStream_t st);
 
