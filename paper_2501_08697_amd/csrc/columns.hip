@@ -9,14 +9,15 @@ namespace apw {
 // transform's tasks wrap around. C is the widest divisor of N2 that the threads and LDS allow:
 // at 120^3 30 columns took 44.9 ms of plane passes per call of 4,096 bands, 24 took 48.1 and
 // 20 took 55 (shorter chunks leave threads without a task in F).
-PlaneShape plane_shape(const Plan &P) {
+PlaneShape plane_shape(const Plan &P, int fft_prec) {
     PlaneShape s{0, 0, P.N2 | 1, 0};
     int a1, b1, a2, b2;
     if (!lds_split_host(P.N1, &a1, &b1) || !lds_split_host(P.N2, &a2, &b2)) return s;
     if (P.N1 != P.N2 && !(P.zero_band[0] && P.zero_band[1])) return s;
     const int m1 = std::max(a1, b1), m2 = std::max(a2, b2), nt = plane_threads(P.N1, P.N2);
     auto lds = [&](int C) {
-        return ((size_t)P.nslab * s.ldr + (size_t)(P.N1 - P.nslab) * C + P.N1 + P.N2 + 1) * sizeof(z64);
+        return ((size_t)P.nslab * s.ldr + (size_t)(P.N1 - P.nslab) * C + P.N1 + P.N2 + 1) *
+               (fft_prec == 0 ? sizeof(z64) : sizeof(c32));
     };
     for (int C = std::min(P.N2, nt / m1); C >= 1; --C)
         if (P.N2 % C == 0 && lds(C) <= 160 * 1024) {
@@ -38,34 +39,48 @@ static int z_bands(const ColumnsCall &c, int ngrp) {
     return std::min(bpw, c.ba.bbt);
 }
 
-template <int N> static int launch_z_inv(const ColumnsCall &c, const void *psi, const double *v) {
+template <int N, typename T> static int launch_z_inv(const ColumnsCall &c, const void *psi, const double *v) {
     const Plan &P = *c.P;
     const int ngrp = ceil_div(P.max_ncol, ZTile<N>::C), bpw = z_bands(c, ngrp);
     const int nblk = ngrp * c.nkb * ceil_div(c.ba.bbt, bpw);
     const int nvt = v ? P.N1 * ceil_div(P.N2, kVtTile) * ceil_div(P.N3, kVtTile) : 0;
-    auto kernel = P.zero_band[2] ? k_z_inv<N, double, double, true> : k_z_inv<N, double, double, false>;
+    auto kernel = P.zero_band[2] ? k_z_inv<N, T, T, true> : k_z_inv<N, T, T, false>;
+    const void *tw = sizeof(T) == 8 ? P.tw64[2] : P.tw32[2];
     KernelTimer kt("z_inv", c.st);
-    hipLaunchKernelGGL(kernel, dim3(nblk + nvt), dim3(ZTile<N>::NT), 0, c.st, static_cast<const z64 *>(psi),
-                       P.kdesc + c.k0, c.ba, static_cast<const z64 *>(P.tw64[2]), static_cast<z64 *>(c.col), P.ldc,
-                       ngrp, bpw, nblk, v, static_cast<double *>(c.vt), P.N1, P.N2);
+    hipLaunchKernelGGL(kernel, dim3(nblk + nvt), dim3(ZTile<N>::NT), 0, c.st, static_cast<const cx<T> *>(psi),
+                       P.kdesc + c.k0, c.ba, static_cast<const cx<T> *>(tw), static_cast<cx<T> *>(c.col), P.ldc,
+                       ngrp, bpw, nblk, v, static_cast<T *>(c.vt), P.N1, P.N2);
     return check_launch("z_inv");
 }
 
-template <int N> static int launch_z_fwd(const ColumnsCall &c, const void *psi, void *hpsi) {
+template <int N, typename T> static int launch_z_fwd(const ColumnsCall &c, const void *psi, void *hpsi) {
     const Plan &P = *c.P;
     const int ngrp = ceil_div(P.max_ncol, ZTile<N>::C), bpw = z_bands(c, ngrp);
-    auto kernel = P.zero_band[2] ? k_z_fwd<N, double, double, true> : k_z_fwd<N, double, double, false>;
+    auto kernel = P.zero_band[2] ? k_z_fwd<N, T, T, true> : k_z_fwd<N, T, T, false>;
+    const void *tw = sizeof(T) == 8 ? P.tw64[2] : P.tw32[2];
     KernelTimer kt("z_fwd", c.st);
     hipLaunchKernelGGL(kernel, dim3(ngrp * c.nkb * ceil_div(c.ba.bbt, bpw)), dim3(ZTile<N>::NT), 0, c.st,
-                       static_cast<const z64 *>(c.col), P.ldc, P.kdesc + c.k0, c.ba,
-                       static_cast<const z64 *>(P.tw64[2]), static_cast<const z64 *>(psi), static_cast<z64 *>(hpsi),
-                       1.0 / (double)P.N, ngrp, bpw);
+                       static_cast<const cx<T> *>(c.col), P.ldc, P.kdesc + c.k0, c.ba,
+                       static_cast<const cx<T> *>(tw), static_cast<const cx<T> *>(psi),
+                       static_cast<cx<T> *>(hpsi), 1.0 / (double)P.N, ngrp, bpw);
     return check_launch("z_fwd");
+}
+
+// FP32 only below kColumnsF32
+template <int N> static int z_inv(const ColumnsCall &c, const void *psi, const double *v) {
+    if constexpr (N < kColumnsF32)
+        if (c.prec == 1) return launch_z_inv<N, float>(c, psi, v);
+    return launch_z_inv<N, double>(c, psi, v);
+}
+template <int N> static int z_fwd(const ColumnsCall &c, const void *psi, void *hpsi) {
+    if constexpr (N < kColumnsF32)
+        if (c.prec == 1) return launch_z_fwd<N, float>(c, psi, hpsi);
+    return launch_z_fwd<N, double>(c, psi, hpsi);
 }
 
 int columns_inverse(const ColumnsCall &c, const void *psi, const double *v) {
     switch (c.P->N3) {
-#define APW_CASE(n) case n: return launch_z_inv<n>(c, psi, v);
+#define APW_CASE(n) case n: return z_inv<n>(c, psi, v);
         APW_LENGTHS(APW_CASE)
 #undef APW_CASE
         default:
@@ -75,7 +90,7 @@ int columns_inverse(const ColumnsCall &c, const void *psi, const double *v) {
 
 int columns_forward(const ColumnsCall &c, const void *psi, void *hpsi) {
     switch (c.P->N3) {
-#define APW_CASE(n) case n: return launch_z_fwd<n>(c, psi, hpsi);
+#define APW_CASE(n) case n: return z_fwd<n>(c, psi, hpsi);
         APW_LENGTHS(APW_CASE)
 #undef APW_CASE
         default:
@@ -84,6 +99,7 @@ int columns_forward(const ColumnsCall &c, const void *psi, void *hpsi) {
 }
 
 int columns_plane(const ColumnsCall &c) {
+    if (c.prec == 1) return columns_plane_f32(c);
     switch (c.P->N1) {
 #define APW_CASE(n) case n: return columns_plane_n1<n>(c);
         APW_LENGTHS(APW_CASE)

@@ -575,9 +575,10 @@ struct ColumnsCall {
     const Plan *P;
     int k0, nkb;
     BatchArgs ba;
-    void *col;          // [nkb bbt][N3][ldc] complex128
+    void *col;          // [nkb bbt][N3][ldc] complex128 (complex64 in FP32)
     void *vt;           // V transposed
     hipStream_t st;
+    int prec = 0;       // transforms, psi and H psi: 0 FP64, 1 FP32
 };
 
 // Chunk width and threads of k_plane, and its LDS bytes; C = 0 when the plane does not fit
@@ -586,7 +587,7 @@ struct PlaneShape {
     int C, NT, ldr;
     size_t lds;
 };
-PlaneShape plane_shape(const Plan &P);
+PlaneShape plane_shape(const Plan &P, int fft_prec);
 
 int columns_inverse(const ColumnsCall &c, const void *psi, const double *v);
 int columns_plane(const ColumnsCall &c);
@@ -598,6 +599,9 @@ bool columns_density_fits(const Plan &P);
 int columns_density_groups(const Plan &P, int nvb);
 int columns_density(const ColumnsCall &c, const double *occ, double *part, int G, int first);
 int columns_density_sum(const Plan &P, const double *part, int G, double *rho, hipStream_t st);
+// columns_plane in FP32: equal x and y lengths below kColumnsF32 (local_uses_columns has the reason)
+constexpr int kColumnsF32 = 90;
+int columns_plane_f32(const ColumnsCall &c);
 // columns_plane for the grids with x length N1 (instantiated in columns_plane_*.hip)
 template <int N1> int columns_plane_n1(const ColumnsCall &c);
 

@@ -24,10 +24,11 @@ inline int plane_bands(int n3, int nvb, int slots) {
     return std::min(best, nvb);
 }
 
-template <int N1, int N2, bool ZB> static int launch_plane(const ColumnsCall &c) {
+template <int N1, int N2, bool ZB, typename T = double> static int launch_plane(const ColumnsCall &c) {
     const Plan &P = *c.P;
-    const PlaneShape sh = plane_shape(P);
-    auto kernel = k_plane<N1, N2, double, ZB>;
+    constexpr int prec = sizeof(T) == 8 ? 0 : 1;
+    const PlaneShape sh = plane_shape(P, prec);
+    auto kernel = k_plane<N1, N2, T, ZB>;
     static bool once = false;
     if (!once) {
         APW_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -38,10 +39,11 @@ template <int N1, int N2, bool ZB> static int launch_plane(const ColumnsCall &c)
     const int per_cu = std::max(1, std::min((int)(160 * 1024 / sh.lds), 512 / sh.NT));
     const int bpw = std::min(nvb, g_x_bands > 0 ? g_x_bands : plane_bands(P.N3, nvb, 256 * per_cu));
     const int ngrp = ceil_div(nvb, bpw);
-    PlaneArgs a{P.kdesc + c.k0, c.vt, P.tw64[0], P.tw64[1], P.xrow, P.nslab, P.ldc, sh.ldr, P.N3, nvb, c.ba.bbt, bpw,
+    const void *const *tw = prec == 0 ? P.tw64 : P.tw32;
+    PlaneArgs a{P.kdesc + c.k0, c.vt, tw[0], tw[1], P.xrow, P.nslab, P.ldc, sh.ldr, P.N3, nvb, c.ba.bbt, bpw,
                 ngrp, sh.C};
     KernelTimer kt("plane", c.st);
-    hipLaunchKernelGGL(kernel, dim3(P.N3 * ngrp), dim3(sh.NT), sh.lds, c.st, static_cast<z64 *>(c.col), a);
+    hipLaunchKernelGGL(kernel, dim3(P.N3 * ngrp), dim3(sh.NT), sh.lds, c.st, static_cast<cx<T> *>(c.col), a);
     return check_launch("plane");
 }
 

@@ -129,7 +129,7 @@ void hwork_sizes(const Plan &P, int prec, int nb, int k0, int k1, size_t sz[kHWo
     const int fft_prec = prec == ABACUS_PW_FP64 ? 0 : 1;
     const int gemm_prec = prec == ABACUS_PW_FP64 ? 0 : 1;
     for (int i = 0; i < kHWorkParts; ++i) sz[i] = 0;
-    sz[0] = local_work_bytes(P, fft_prec, k1 - k0, nb);
+    sz[0] = local_work_bytes(P, fft_prec, prec == ABACUS_PW_FP32 ? 1 : 0, k1 - k0, nb);
     if (P.nproj == 0) return;
     const size_t gb = gemm_prec == 0 ? 16 : 8;
     sz[1] = (size_t)nb * P.nproj * gb * (k1 - k0);
@@ -178,8 +178,9 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
             }
     }
     void *slab = w[0], *projq = w[1], *gemm_part = w[2], *psibf = w[3], *qbf = w[4], *tmp_io = w[5];
-    if (refresh_copies) APW_TRY(operator_copies(p, P, fft_prec == 1, gemm_prec == 1 && !bf, st, bf));
-    const void *v = fft_prec == 0 ? static_cast<const void *>(p.vloc) : P.vloc32.ptr;
+    const bool v64 = fft_prec == 0 || local_uses_columns(P, fft_prec, io_prec);   // the column passes convert V themselves
+    if (refresh_copies) APW_TRY(operator_copies(p, P, !v64, gemm_prec == 1 && !bf, st, bf));
+    const void *v = v64 ? static_cast<const void *>(p.vloc) : P.vloc32.ptr;
     if (P.nproj == 0) return local_term(P, k0, k1, fft_prec, io_prec, v, psi, hpsi, nb, slab, st);
 
     const size_t gb = gemm_prec == 0 ? 16 : 8;   // bytes per element of Q (complex64 in the BF16 mode)

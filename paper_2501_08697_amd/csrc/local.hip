@@ -1,7 +1,8 @@
 // Local-potential term of H psi on the real-space grid (plane-wave KS equation,
 // Sec. III.A; V_local of the pseudopotential split, Sec. II.A). FP64 runs the column passes of
-// columns.hpp wherever a plane fits them; this file holds the passes over whole grid planes that
-// FP32 and the mixed modes, the density and the adjoint use, and FP64 where it does not:
+// columns.hpp wherever a plane fits them, and so does FP32 on smaller grids
+// (local_uses_columns) and the density where it has a kernel; this file holds the passes over whole
+// grid planes that the gradient of V and everything else use:
 //
 //   (V psi)(G) = (1/N) sum_j e^{-iG.r_j} V(r_j) sum_{G'} psi(G') e^{+iG'.r_j}
 //
@@ -1202,20 +1203,25 @@ int local_sum_parts(const Plan &P, const double *part, int G, double scale, doub
 // Whether the call's planes run through the column passes (columns.hpp): FP64 in the automatic
 // plane mode, a plane that fits in LDS, and a kernel for the pair of lengths. They took the
 // FP64 local term at 72^3 (128 bands) from 461 to 345 us, at 120^3 (4,096 bands) from 78.9 to
-// 58.6 ms. In FP32 the plane pass is bound by VALU instructions, which are as many as in FP64
-// (144 of 245 us at 72^3): 216 against 243 us there, but 16.2 against 13.9 ms at 128^3, so FP32
-// keeps the slab passes.
-static bool use_columns(const Plan &P, int fft_prec) {
-    return fft_prec == 0 && g_yz_mode == 0 && plane_shape(P).C > 0;
+// 58.6 ms. In FP32 the plane pass is bound by VALU instructions, which are as many as in FP64:
+// H psi with two atoms took 47.5 us against 56.2 through the slab passes at 32^3 x 64 bands, 84.9
+// against 127 at 48^3 x 96, 251 against 268 at 72^3 x 128 and 356 against 386 at 81^3 x 128, but 1151
+// against 1106 at 90^3 x 256, and the local term 16.2 against 13.9 ms at 128^3. So FP32 takes the
+// column passes on equal x and y lengths below kColumnsF32. The mixed modes, whose results are
+// complex128, keep the slab passes: the columns transform the axes in another order, which moves
+// FP32 roundings (2e-9 of H psi) that those results would show.
+bool local_uses_columns(const Plan &P, int fft_prec, int io_prec) {
+    if (fft_prec == 1 && (io_prec == 0 || P.N1 != P.N2 || P.N1 >= kColumnsF32)) return false;
+    return g_yz_mode == 0 && plane_shape(P, fft_prec).C > 0;
 }
 
 static size_t column_bytes(const Plan &P, int fft_prec) {
     return (size_t)P.N3 * P.ldc * (fft_prec == 0 ? 16 : 8);
 }
 
-int local_band_batch(const Plan &P, int fft_prec, int nkb, int nb) {
+int local_band_batch(const Plan &P, int fft_prec, int io_prec, int nkb, int nb) {
     if (g_band_batch > 0) return std::min(g_band_batch, nb);
-    if (!use_columns(P, fft_prec)) return std::min(64, nb);
+    if (!local_uses_columns(P, fft_prec, io_prec)) return std::min(64, nb);
     // as many bands as 4 GiB of columns hold: at 120^3 x 8 k-points the plane passes of a call took
     // 39.5 ms with 4 GiB, 41.9 with 1 GiB and 42.5 with 192 MiB (batches that stay in the 256 MB
     // infinity cache gain nothing back; every launch's last round of work-groups costs)
@@ -1223,15 +1229,15 @@ int local_band_batch(const Plan &P, int fft_prec, int nkb, int nb) {
     return (int)std::max<size_t>(1, std::min<size_t>(nb, (size_t(4) << 30) / per));
 }
 
-// The density of every band and k-point (occ [nk][nb]) through the column passes, where use_columns
-// holds and the plane kernel exists: at 72^3 x 128 bands 40 us of z pass and 146 of plane pass (the
+// The density of every band and k-point (occ [nk][nb]) through the column passes, where
+// local_uses_columns holds and the plane kernel exists: at 72^3 x 128 bands 40 us of z pass and 146 of plane pass (the
 // plane pass bound by its transforms, as k_plane), where the slab passes took 145 and 101.
 bool local_density_columns(const Plan &P, int fft_prec) {
-    return use_columns(P, fft_prec) && columns_density_fits(P);
+    return fft_prec == 0 && local_uses_columns(P, 0, 0) && columns_density_fits(P);
 }
 
 int local_density_by_columns(Plan &P, int nb, const void *psi, const double *occ, double *rho, hipStream_t st) {
-    const int bb = local_band_batch(P, 0, P.nk, nb), G = columns_density_groups(P, P.nk * bb);
+    const int bb = local_band_batch(P, 0, 0, P.nk, nb), G = columns_density_groups(P, P.nk * bb);
     APW_TRY(P.slab.ensure(column_bytes(P, 0) * P.nk * bb));
     APW_TRY(P.gradv_part.ensure(sizeof(double) * (size_t)G * P.N));
     double *part = P.gradv_part.as<double>();
@@ -1244,9 +1250,9 @@ int local_density_by_columns(Plan &P, int nb, const void *psi, const double *occ
     return columns_density_sum(P, part, G, rho, st);
 }
 
-size_t local_work_bytes(const Plan &P, int fft_prec, int nkb, int nb) {
-    const int nvb = nkb * local_band_batch(P, fft_prec, nkb, nb);
-    if (!use_columns(P, fft_prec)) return local_slab_bytes(P, fft_prec, nvb);
+size_t local_work_bytes(const Plan &P, int fft_prec, int io_prec, int nkb, int nb) {
+    const int nvb = nkb * local_band_batch(P, fft_prec, io_prec, nkb, nb);
+    if (!local_uses_columns(P, fft_prec, io_prec)) return local_slab_bytes(P, fft_prec, nvb);
     return (column_bytes(P, fft_prec) * nvb + 255) / 256 * 256 + (size_t)P.N * (fft_prec == 0 ? 8 : 4);
 }
 
@@ -1261,13 +1267,13 @@ static int slab_batch(const Plan &P, int k0, int nkb, const BatchArgs &ba, const
 int local_term(const Plan &P, int k0, int k1, int fft_prec, int io_prec, const void *vloc, const void *psi,
                void *hpsi, int nb, void *slab, hipStream_t st, const std::function<int(int, int)> &after_batch) {
     const int nkb = k1 - k0;
-    const int band_batch = local_band_batch(P, fft_prec, nkb, nb);
-    const bool cols = use_columns(P, fft_prec);
+    const int band_batch = local_band_batch(P, fft_prec, io_prec, nkb, nb);
+    const bool cols = local_uses_columns(P, fft_prec, io_prec);
     char *vt = static_cast<char *>(slab) + (column_bytes(P, fft_prec) * nkb * band_batch + 255) / 256 * 256;
     const double *v64 = static_cast<const double *>(vloc);
     for (int b0 = 0; b0 < nb; b0 += band_batch) {
         const BatchArgs ba{nb, P.pw_off[k0], b0, std::min(band_batch, nb - b0)};
-        const ColumnsCall c{&P, k0, nkb, ba, slab, vt, st};
+        const ColumnsCall c{&P, k0, nkb, ba, slab, vt, st, fft_prec};
         if (cols) {
             APW_TRY(columns_inverse(c, psi, b0 == 0 ? v64 : nullptr));
             APW_TRY(columns_plane(c));

@@ -11,17 +11,19 @@ namespace apw {
 int local_length_supported(int n);
 // OK when the plan's grid can run at fft_prec (0 = FP64, 1 = FP32), else EBAD_FFT_SIZE.
 int local_supported(const Plan &P, int fft_prec);
+// Whether the local term runs the column passes (columns.hpp).
+bool local_uses_columns(const Plan &P, int fft_prec, int io_prec);
 // Slab work space for nbands bands.
 size_t local_slab_bytes(const Plan &P, int fft_prec, int nbands);
 
 // Bands per batch of the local term over nkb k-points, and its work space.
-int local_band_batch(const Plan &P, int fft_prec, int nkb, int nb);
-size_t local_work_bytes(const Plan &P, int fft_prec, int nkb, int nb);
+int local_band_batch(const Plan &P, int fft_prec, int io_prec, int nkb, int nb);
+size_t local_work_bytes(const Plan &P, int fft_prec, int io_prec, int nkb, int nb);
 
 // hpsi = |k+G|^2 psi + (V psi) for nb bands at the k-points [k0, k1): psi and hpsi start at
 // k0's [nb][npw_k] block, k blocks back to back. Each band batch runs every k-point in one
 // launch per pass. fft_prec: 0 FP64, 1 FP32 transforms. io_prec: 0 complex128, 1 complex64.
-// vloc: float64 grid for fft_prec 0, float32 for 1. slab: local_work_bytes.
+// vloc: float64 grid for fft_prec 0 or the column passes, else float32. slab: local_work_bytes.
 // after_batch(b0, bbt), if given, is called once the kernels of bands [b0, b0+bbt)
 // are enqueued (their H psi rows are complete when that work has run on st).
 int local_term(const Plan &P, int k0, int k1, int fft_prec, int io_prec, const void *vloc, const void *psi,
