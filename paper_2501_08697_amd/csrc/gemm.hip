@@ -724,9 +724,9 @@ int gemm_nn_tri(int M, int G, const void *A, int64_t lda, const void *B, int64_t
     return gemm_nn_batch_t<double, double>(M, M, &pr, 1, A, lda, B, C, 1.0, 0.0, st, 1);
 }
 
-int gemm_nn_f32_into_f64(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
-                         int64_t ldc, double alpha, double beta, hipStream_t st) {
-    return gemm_nn_t<float, double>(M, G, K, A, lda, B, ldb, C, ldc, alpha, beta, st);
+int gemm_nn_f32_into_f64(int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B, void *C,
+                         double alpha, double beta, hipStream_t st) {
+    return gemm_nn_batch_t<float, double>(M, K, pr, np, A, lda, B, C, alpha, beta, st);
 }
 
 int reduce_dapply_f32(int M, int N, int nsplit, const void *part, const double *dmat, const int *blo, const int *bn,

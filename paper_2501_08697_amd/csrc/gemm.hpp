@@ -62,9 +62,9 @@ int gemm_nn_tri(int M, int G, const void *A, int64_t lda, const void *B, int64_t
 int gemm_nn_f32_of_f64(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                        int64_t ldc, double alpha, double beta, hipStream_t st);
 
-// As gemm_nn with complex64 A and B accumulated into a complex128 C.
-int gemm_nn_f32_into_f64(int M, int G, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
-                         int64_t ldc, double alpha, double beta, hipStream_t st);
+// As gemm_nn_batch with complex64 A and B accumulated into a complex128 C.
+int gemm_nn_f32_into_f64(int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B, void *C,
+                         double alpha, double beta, hipStream_t st);
 
 // part[tile][i][al] = sum over the tile's g of kg[g][al] Im(beta[i][g] conj(X[i][g])) with
 // X[i][g] = sum_n W[n][i] psi[n][g]: W [nb][M], psi [nb][G], beta [M][G], kg [G][3]; tiles of

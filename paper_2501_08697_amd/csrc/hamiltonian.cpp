@@ -232,7 +232,7 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
     }
     // hpsi[b0 .. b0+bbt) += B_k Q_k[b0 .. b0+bbt) for every k-point
     auto add_bq = [&](int b0, int bbt, hipStream_t s) -> int {
-        const int step = bf || prec == ABACUS_PW_MIXED_FP32 ? 1 : kGemmMaxBatch;
+        const int step = bf ? 1 : kGemmMaxBatch;
         for (int k = k0; k < k1; k += step) {
             const KTables &K = P.k[k];
             char *yk = static_cast<char *>(hpsi) + ((size_t)nb * (K.pw_off - P.pw_off[k0]) + (size_t)b0 * K.npw) * ib;
@@ -244,8 +244,6 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
                 const uint32_t *btk = P.betabfT.as<uint32_t>() + (size_t)ldq * K.pw_off;
                 APW_TRY(gemm_nn_bf16_into_f64(bbt, K.npw, P.nproj, qbf, ldq, btk, ldq, yk, K.npw, s));
             }
-            else if (prec == ABACUS_PW_MIXED_FP32)
-                APW_TRY(gemm_nn_f32_into_f64(bbt, K.npw, P.nproj, qb, P.nproj, bk, K.npw, yk, K.npw, 1.0, 1.0, s));
             else {
                 NnProduct pr[kGemmMaxBatch];
                 const int np = std::min(step, k1 - k);
@@ -255,7 +253,9 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
                     pr[i] = NnProduct{Ki.npw, Ki.npw, Ki.npw, (int64_t)i * nb * P.nproj, o * P.nproj,
                                       o * nb + (int64_t)b0 * (Ki.npw - K.npw)};
                 }
-                APW_TRY(gemm_nn_batch(gemm_prec, bbt, P.nproj, pr, np, qb, P.nproj, bk, yk, 1.0, 1.0, s));
+                if (prec == ABACUS_PW_MIXED_FP32)
+                    APW_TRY(gemm_nn_f32_into_f64(bbt, P.nproj, pr, np, qb, P.nproj, bk, yk, 1.0, 1.0, s));
+                else APW_TRY(gemm_nn_batch(gemm_prec, bbt, P.nproj, pr, np, qb, P.nproj, bk, yk, 1.0, 1.0, s));
             }
         }
         return ABACUS_PW_OK;
