@@ -74,7 +74,7 @@ int apply_h_backward_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, 
 // the unnormalised inverse transform of the coefficients. Per band batch the y-z
 // inverse transforms of every k-point write slab planes, then one x pass
 // transforms them and adds the weighted squared moduli; the G partial grids are
-// summed in a fixed order at the end.
+// summed in a fixed order at the end. In FP64 the column passes do the same where they have a kernel.
 int density_all(const abacus_pw_problem &p, Plan &P, int prec, int nb, const void *psi, const double *occ,
                 double *rho, hipStream_t st) {
     (void)p;
