@@ -609,8 +609,9 @@ def c2_times(B, dev, prob, dp, x64, steps):
 def density_times(B, W, dev, prob, dp, x, steps):
     """Band density rho(r) = sum_n w_n |psi_n(r)|^2 of the benchmark's 128 bands on its 72^3 grid, FP64.
 
-    Per call: the y-z inverse passes (sphere -> slab planes) and one x pass that
-    transforms and accumulates (k_density_x), then the fixed-order sum of the
+    Per call: the inverse z pass to columns and a plane pass that transforms and
+    accumulates (z_inv, density_plane), or, where the plane mode asks for slabs, the y-z
+    inverse passes and one x pass (k_density_x); then the fixed-order sum of the
     partial grids. The model bytes are the inverse half of the pruned 5-pass
     local-term model plus rho written once: nb (cb N 2 (f_disk + f_slab) + cb npw) + 8 N.
     k_density_x moves nb cb S (slab in) plus its partial grids (G = 8 of N doubles,
