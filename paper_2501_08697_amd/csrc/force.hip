@@ -25,7 +25,8 @@ namespace {
 
 constexpr int kMaxAtomProj = 16;   // projectors per atom handled by the reduction
 
-// W[n][i] = occ[n] conj(sum_j D_ij P[n][j]) (P, W [nb][nproj]); the D-block tables of the plan.
+// W[n][i] = occ[n] conj(sum_j D_ij P[n][j]) (P, W [nb][nproj]); the D-block tables of the plan. Only for
+// more projectors than proj_weights takes (it forms W as it sums the splits, one launch instead of two).
 __global__ __launch_bounds__(256) void k_force_w(int nb, int nproj, const z64 *__restrict__ P,
                                                  const double *__restrict__ occ, const double *__restrict__ dmat,
                                                  const int *__restrict__ blo, const int *__restrict__ bn,
@@ -113,7 +114,7 @@ int force_nl_all(const abacus_pw_problem &p, Plan &P, int nb, const void *psi, c
     const double *kg_all = P.force_tab.as<double>();
     const int *aoff = reinterpret_cast<const int *>(P.force_tab.as<char>() + sizeof(double) * 3 * (size_t)P.npw_total);
     const size_t pq = sizeof(z64) * (size_t)P.nproj * nb;
-    APW_TRY(P.proj.ensure(pq));
+    if (!proj_weights_fit(P.nproj)) APW_TRY(P.proj.ensure(pq));
     APW_TRY(P.proj2.ensure(pq));
     APW_TRY(P.gemm_part.ensure(std::max(gemm_cn_part_bytes(P.nproj, nb, P.max_npw, 16, g_splitk_chunk),
                                         sizeof(double) * 3 * (size_t)P.nproj * force_contract_tiles(P.max_npw))));
@@ -121,9 +122,13 @@ int force_nl_all(const abacus_pw_problem &p, Plan &P, int nb, const void *psi, c
         const KTables &K = P.k[k];
         const z64 *bk = static_cast<const z64 *>(p.beta) + (size_t)P.nproj * K.pw_off;
         const z64 *xk = static_cast<const z64 *>(psi) + (size_t)nb * K.pw_off;
-        APW_TRY(gemm_cn(0, P.nproj, nb, K.npw, bk, K.npw, xk, K.npw, P.proj.ptr, P.nproj, 1.0, 0.0, P.gemm_part.ptr,
-                        g_splitk_chunk, st));
-        {
+        if (proj_weights_fit(P.nproj)) {
+            APW_TRY(proj_weights(P.nproj, nb, K.npw, bk, xk, occ + (size_t)k * nb, static_cast<const double *>(p.dmat),
+                                 P.proj_blk_lo, P.proj_blk_n, P.proj_blk_doff, P.proj2.ptr, P.gemm_part.ptr,
+                                 g_splitk_chunk, st));
+        } else {
+            APW_TRY(gemm_cn(0, P.nproj, nb, K.npw, bk, K.npw, xk, K.npw, P.proj.ptr, P.nproj, 1.0, 0.0, P.gemm_part.ptr,
+                            g_splitk_chunk, st));
             KernelTimer kt("force_w", st);
             hipLaunchKernelGGL(k_force_w, dim3((unsigned)ceil_div64((int64_t)nb * P.nproj, 256)), dim3(256), 0, st, nb,
                                P.nproj, P.proj.as<z64>(), occ + (size_t)k * nb, static_cast<const double *>(p.dmat),

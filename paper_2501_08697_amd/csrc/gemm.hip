@@ -243,7 +243,8 @@ static int launch_reduce(int M, int N, int nsplit, const void *part, void *C, in
     return check_launch("gemm_reduce");
 }
 
-// P[j][i] = sum_s part[s][j][i]; Q[j][i] = sum_t D_blk(i)[i - lo][t] P[j][lo + t]
+// P[j][i] = sum_s part[s][j][i]; Q[j][i] = sum_t D_blk(i)[i - lo][t] P[j][lo + t], with occ (one product
+// only) occ[j] times its conjugate instead.
 // One work-group per band j. The splits are divided among G thread groups
 // (G M <= blockDim.x), each thread summing its splits in four independent
 // chains; the group sums are added in a fixed order, so the result does not
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, RedBatch r
                                                                int N, const double *__restrict__ dmat,
                                                                const int *__restrict__ blo, const int *__restrict__ bn,
                                                                const int *__restrict__ bdoff, cx<T> *__restrict__ P,
-                                                               cx<T> *__restrict__ Q) {
+                                                               cx<T> *__restrict__ Q, const double *__restrict__ occ) {
     extern __shared__ __align__(16) unsigned char smem[];
     cx<double> *pl = reinterpret_cast<cx<double> *>(smem);   // [G][M] group sums, then the total in [0][M]
     const int j = blockIdx.x, pb = blockIdx.y, nsplit = rb.z0[pb + 1] - rb.z0[pb];
@@ -307,6 +308,10 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, RedBatch r
         for (int t = 0; t < n; ++t) {
             re += d[t] * pl[lo + t].re;
             im += d[t] * pl[lo + t].im;
+        }
+        if (occ) {
+            re *= occ[j];
+            im *= -occ[j];
         }
         Q[(int64_t)j * M + i] = cx<T>{(T)re, (T)im};
     }
@@ -670,19 +675,32 @@ int gemm_cn_herm(int M, int K, const void *A, int64_t lda, void *C, int64_t ldc,
     return gemm_cn_t<double>(M, M, K, A, lda, A, lda, C, ldc, 1.0, 0.0, part, 0, st, 1);
 }
 
+// LDS of k_reduce_dapply: the group sums of a band. M above 4096 exceeds the limit.
+constexpr size_t kDapplyLds = 64 * 1024;
+static size_t dapply_lds(int M) { return (size_t)reduce_groups(M) * M * sizeof(z64); }
+
 template <typename T>
 static int proj_dapply_t(int M, int N, const CnProduct *pr, int np, const void *Bm, const void *psi,
                          const double *dmat, const int *blo, const int *bn, const int *bdoff, void *P, void *Q,
-                         void *part, int chunk_hint, bool wide, hipStream_t st) {
+                         void *part, int chunk_hint, bool wide, hipStream_t st, const double *occ = nullptr) {
     if (M <= 0 || N <= 0) return ABACUS_PW_OK;
     RedBatch rb;
     APW_TRY(cn_part<T>(M, N, pr, np, Bm, psi, part, chunk_hint, wide, &rb, st));
-    const size_t lds = (size_t)reduce_groups(M) * M * sizeof(cx<double>);
-    if (lds > 64 * 1024) return set_error(ABACUS_PW_EBAD_SHAPE, "too many projectors for the D-apply stage");
+    const size_t lds = dapply_lds(M);
+    if (lds > kDapplyLds) return set_error(ABACUS_PW_EBAD_SHAPE, "too many projectors for the D-apply stage");
     KernelTimer kt("reduce_dapply", st);
     hipLaunchKernelGGL(k_reduce_dapply<T>, dim3(N, np), dim3(kRedThreads), lds, st, M, rb, static_cast<const cx<T> *>(part), N,
-                       dmat, blo, bn, bdoff, static_cast<cx<T> *>(P), static_cast<cx<T> *>(Q));
+                       dmat, blo, bn, bdoff, static_cast<cx<T> *>(P), static_cast<cx<T> *>(Q), occ);
     return check_launch("reduce_dapply");
+}
+
+bool proj_weights_fit(int M) { return dapply_lds(M) <= kDapplyLds; }
+
+int proj_weights(int M, int N, int K, const void *Bm, const void *psi, const double *occ, const double *dmat,
+                 const int *blo, const int *bn, const int *bdoff, void *W, void *part, int chunk_hint, hipStream_t st) {
+    const CnProduct pr{K, K, K, 0, 0};
+    return proj_dapply_t<double>(M, N, &pr, 1, Bm, psi, dmat, blo, bn, bdoff, nullptr, W, part, chunk_hint, false, st,
+                                 occ);
 }
 
 int proj_dapply(int prec, int M, int N, const CnProduct *pr, int np, const void *Bm, const void *psi,
@@ -757,14 +775,15 @@ int gemm_nn_f32_into_f64(int M, int K, const NnProduct *pr, int np, const void *
 
 int reduce_dapply_f32(int M, int N, int nsplit, const void *part, const double *dmat, const int *blo, const int *bn,
                       const int *bdoff, void *Q, hipStream_t st) {
-    const size_t lds = (size_t)reduce_groups(M) * M * sizeof(cx<double>);
-    if (lds > 64 * 1024) return set_error(ABACUS_PW_EBAD_SHAPE, "too many projectors for the D-apply stage");
+    const size_t lds = dapply_lds(M);
+    if (lds > kDapplyLds) return set_error(ABACUS_PW_EBAD_SHAPE, "too many projectors for the D-apply stage");
     KernelTimer kt("reduce_dapply", st);
     RedBatch rb;
     rb.z0[0] = 0;
     rb.z0[1] = nsplit;
     hipLaunchKernelGGL(k_reduce_dapply<float>, dim3(N), dim3(kRedThreads), lds, st, M, rb, static_cast<const c32 *>(part),
-                       N, dmat, blo, bn, bdoff, static_cast<c32 *>(nullptr), static_cast<c32 *>(Q));
+                       N, dmat, blo, bn, bdoff, static_cast<c32 *>(nullptr), static_cast<c32 *>(Q),
+                       static_cast<const double *>(nullptr));
     return check_launch("reduce_dapply");
 }
 

@@ -38,14 +38,20 @@ int proj_dapply(int prec, int M, int N, const CnProduct *pr, int np, const void 
                 const double *dmat, const int *blo, const int *bn, const int *bdoff, void *P, void *Q, void *part,
                 int chunk_hint, bool wide, hipStream_t st);
 
-// C[j*ldc + g] = alpha * sum_i A[j*lda + i] B[i*ldb + g] + beta * C[...],  j < M, g < G.
+// W[j][i] = occ[j] conj(Q[j][i]) of one FP64 product (the band weights of the nonlocal force), for M that
+// proj_weights_fit allows.
+bool proj_weights_fit(int M);
+int proj_weights(int M, int N, int K, const void *Bm, const void *psi, const double *occ, const double *dmat,
+                 const int *blo, const int *bn, const int *bdoff, void *W, void *part, int chunk_hint, hipStream_t st);
+
 // gemm_cn on complex128 A, B, C with FP32 products: the operands are rounded to
 // complex64 as they are staged, partial sums are FP32, the split-K sum and C are FP64
 // (the subspace projection of the reduced-precision Davidson phase).
 int gemm_cn_f32_of_f64(int M, int N, int K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                        int64_t ldc, double alpha, double beta, void *part, int chunk_hint, hipStream_t st);
 
-// The same for np products: A [M][lda], B rows of ldb, C rows of ldc, from their offsets.
+// C[j*ldc + g] = alpha * sum_i A[j*lda + i] B[i*ldb + g] + beta * C[...],  j < M, g < G, for np
+// products: A [M][lda], B rows of ldb, C rows of ldc, from their offsets.
 int gemm_nn_batch(int prec, int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
                   void *C, double alpha, double beta, hipStream_t st);
 
