@@ -66,16 +66,16 @@ template <int N, typename T> static int launch_z_fwd(const ColumnsCall &c, const
     return check_launch("z_fwd");
 }
 
-// FP32 only below kColumnsF32
+// FP32 only below kColumnsF32: the FP64 kernel must never see FP32 data.
 template <int N> static int z_inv(const ColumnsCall &c, const void *psi, const double *v) {
-    if constexpr (N < kColumnsF32)
-        if (c.prec == 1) return launch_z_inv<N, float>(c, psi, v);
-    return launch_z_inv<N, double>(c, psi, v);
+    if (c.prec == 0) return launch_z_inv<N, double>(c, psi, v);
+    if constexpr (N < kColumnsF32) return launch_z_inv<N, float>(c, psi, v);
+    return set_error(ABACUS_PW_EINTERNAL, "FP32 z pass without a kernel");
 }
 template <int N> static int z_fwd(const ColumnsCall &c, const void *psi, void *hpsi) {
-    if constexpr (N < kColumnsF32)
-        if (c.prec == 1) return launch_z_fwd<N, float>(c, psi, hpsi);
-    return launch_z_fwd<N, double>(c, psi, hpsi);
+    if (c.prec == 0) return launch_z_fwd<N, double>(c, psi, hpsi);
+    if constexpr (N < kColumnsF32) return launch_z_fwd<N, float>(c, psi, hpsi);
+    return set_error(ABACUS_PW_EINTERNAL, "FP32 z pass without a kernel");
 }
 
 int columns_inverse(const ColumnsCall &c, const void *psi, const double *v) {

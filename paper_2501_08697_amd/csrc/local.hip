@@ -1211,7 +1211,7 @@ int local_sum_parts(const Plan &P, const double *part, int G, double scale, doub
 // complex128, keep the slab passes: the columns transform the axes in another order, which moves
 // FP32 roundings (2e-9 of H psi) that those results would show.
 bool local_uses_columns(const Plan &P, int fft_prec, int io_prec) {
-    if (fft_prec == 1 && (io_prec == 0 || P.N1 != P.N2 || P.N1 >= kColumnsF32)) return false;
+    if (fft_prec == 1 && (io_prec == 0 || P.N1 != P.N2 || P.N1 >= kColumnsF32 || P.N3 >= kColumnsF32)) return false;
     return g_yz_mode == 0 && plane_shape(P, fft_prec).C > 0;
 }
 

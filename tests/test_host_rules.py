@@ -1,0 +1,59 @@
+"""Rules that the library decides on the host, asked of its internal functions by a small program
+that links against it: nothing is launched, so no GPU is needed."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2501_08697_amd import build
+
+PRELUDE = r"""
+#include "columns.hpp"
+#include "gemm.hpp"
+#include "local.hpp"
+#include <cstdio>
+using namespace apw;
+// the fields of a plan that the rules read: a sphere of a quarter of the grid length
+static void fill(Plan &P, int n1, int n2, int n3) {
+    P.N1 = n1; P.N2 = n2; P.N3 = n3;
+    P.N = (int64_t)n1 * n2 * n3;
+    P.nslab = n1 / 2 + 1;
+    P.max_ncol = n1 * n2 / 5;
+    P.ldc = (P.max_ncol + 15) / 16 * 16;
+    P.zero_band[0] = P.zero_band[1] = P.zero_band[2] = true;
+}
+"""
+
+
+@pytest.fixture
+def ask(tmp_path):
+    """Compiles and runs `body` as main; returns the numbers it prints."""
+    def f(body):
+        src, exe = tmp_path / "t.cpp", tmp_path / "t"
+        src.write_text(PRELUDE + "int main() {\n" + body + "\nfflush(stdout); _Exit(0); }\n")
+        libdir = os.path.dirname(build.LIB)
+        r = subprocess.run([build.HIPCC, "--offload-host-only", "-x", "hip", "-std=c++17", "-O1",
+                            f"-I{build.ROOT}/include", f"-I{build.CSRC}", str(src), "-o", str(exe), f"-L{libdir}",
+                            f"-l:{os.path.basename(build.LIB)}", f"-Wl,-rpath,{libdir}"], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return [int(v) for v in subprocess.run([str(exe)], capture_output=True, text=True, check=True,
+                                               timeout=60).stdout.split()]
+    return f
+
+
+def test_fp32_columns_refuse_lengths_without_a_kernel(ask):
+    """An FP32 z pass of a length that has only an FP64 kernel is an internal error (-10), never the FP64
+    kernel on FP32 data, and the rule that chooses the columns looks at all three lengths."""
+    got = ask("""
+    for (int n3 : {90, 96, 128}) {
+        Plan P;
+        fill(P, 72, 72, n3);
+        ColumnsCall c{&P, 0, 1, BatchArgs{1, 0, 0, 1}, nullptr, nullptr, nullptr, 1};
+        printf("%d %d %d\\n", (int)local_uses_columns(P, 1, 1), columns_inverse(c, nullptr, nullptr),
+               columns_forward(c, nullptr, nullptr));
+    }
+    Plan P;
+    fill(P, 72, 72, 72);
+    printf("%d\\n", (int)local_uses_columns(P, 1, 1));
+    """)
+    assert got == [0, -10, -10] * 3 + [1]
