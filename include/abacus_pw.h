@@ -404,7 +404,7 @@ int abacus_pw_profile_read(char *buf, int size);
 /*
  * Tuning knobs, process-wide (the autotuner sets these; 0 = library default).
  * band_batch   bands per local-term batch (work space = band_batch bands of planes or columns; 0: 64
- *              bands of planes, 4 GiB of columns)
+ *              bands of planes; as many bands of columns as 4 GiB hold, with overlap 1 at most 64)
  * splitk_chunk K chunk of the split-K projection GEMM (multiple of 16)
  * yz_bands     bands handled by one y-z plane (or z column) work-group
  * x_bands      bands handled by one x-pass (or x-y plane) work-group

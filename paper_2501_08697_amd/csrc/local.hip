@@ -1224,9 +1224,12 @@ int local_band_batch(const Plan &P, int fft_prec, int io_prec, int nkb, int nb) 
     if (!local_uses_columns(P, fft_prec, io_prec)) return std::min(64, nb);
     // as many bands as 4 GiB of columns hold: at 120^3 x 8 k-points the plane passes of a call took
     // 39.5 ms with 4 GiB, 41.9 with 1 GiB and 42.5 with 192 MiB (batches that stay in the 256 MB
-    // infinity cache gain nothing back; every launch's last round of work-groups costs)
+    // infinity cache gain nothing back; every launch's last round of work-groups costs). With the
+    // overlap knob on, at most the 64 of the slab passes: the side stream accumulates a batch as soon
+    // as it is done, and would otherwise start after the last plane pass.
     const size_t per = column_bytes(P, fft_prec) * nkb;
-    return (int)std::max<size_t>(1, std::min<size_t>(nb, (size_t(4) << 30) / per));
+    const int most = g_overlap == 1 ? std::min(64, nb) : nb;
+    return (int)std::max<size_t>(1, std::min<size_t>(most, (size_t(4) << 30) / per));
 }
 
 // The density of every band and k-point (occ [nk][nb]) through the column passes, where

@@ -57,3 +57,20 @@ def test_fp32_columns_refuse_lengths_without_a_kernel(ask):
     printf("%d\\n", (int)local_uses_columns(P, 1, 1));
     """)
     assert got == [0, -10, -10] * 3 + [1]
+
+
+def test_overlap_keeps_its_batches(ask):
+    """With the projector GEMMs on a second stream the local term runs in batches of at most 64 bands, so
+    that their accumulation can begin; without it the columns take every band that their work space holds."""
+    got = ask("""
+    Plan P;
+    fill(P, 72, 72, 72);
+    for (int ov : {0, 1, 2}) {
+        g_overlap = ov;
+        printf("%d %d\\n", local_band_batch(P, 0, 0, 1, 128), local_band_batch(P, 0, 0, 1, 40));
+    }
+    g_overlap = 1;
+    g_band_batch = 100;
+    printf("%d\\n", local_band_batch(P, 0, 0, 1, 128));
+    """)
+    assert got == [128, 40, 64, 40, 128, 40, 100]
