@@ -612,9 +612,15 @@ size_t gemm_cn_part_bytes(int M, int N, int K, int elem_bytes, int chunk_hint) {
     return std::max(few, many) * elem_bytes;
 }
 
+// A launch takes at most 65,536 work-groups in y and in z (hipDeviceAttributeMaxGridDimY, Z), and the
+// products of a launch add up there: the splits of the projection in z, the column tiles in y.
+constexpr int kMaxGridYZ = 65535;
 int gemm_batch_limit(int M, int N, int K, int elem_bytes, int chunk_hint) {
-    return (int)std::max<size_t>(1, std::min<size_t>(kMaxBatch, kPartCap / gemm_cn_part_bytes(M, N, K, elem_bytes, chunk_hint)));
+    const size_t part = gemm_cn_part_bytes(M, N, K, elem_bytes, chunk_hint);
+    const int splits = chunk_hint > 0 ? ceil_div(K, ceil_div(chunk_hint, KT) * KT) : std::max(512, ceil_div(K, 1024));
+    return (int)std::max<size_t>(1, std::min<size_t>({kMaxBatch, kPartCap / part, (size_t)(kMaxGridYZ / splits)}));
 }
+int gemm_nn_batch_limit(int G) { return std::max(1, std::min(kMaxBatch, kMaxGridYZ / ceil_div(G, TN))); }
 
 template <typename T, typename TS = T>
 static int cn_part(int M, int N, const CnProduct *pr, int np, const void *A, const void *B, void *part,

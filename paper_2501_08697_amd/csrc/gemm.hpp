@@ -27,9 +27,11 @@ struct NnProduct {
     int G;
     int64_t ldb, ldc, a, b, c;
 };
-// Products of that shape (K at most) one launch may take: kGemmMaxBatch, and partial sums of at
-// most 1 GiB (gemm_cn_part_bytes each).
+// Products of that shape (K at most) one launch may take: kGemmMaxBatch, partial sums of at most
+// 1 GiB (gemm_cn_part_bytes each), and the splits that a grid holds.
 int gemm_batch_limit(int M, int N, int K, int elem_bytes, int chunk_hint);
+// Products with G columns at most that one gemm_nn_batch may take.
+int gemm_nn_batch_limit(int G);
 
 // For every product p: P[j][i] = <beta_i | psi_j> (M = nproj, N = bands, K = npw);
 // Q[j][i] = sum_t D_blk(i) P[j][.], P and Q [np][N][M]. P may be NULL. D-block tables as in the

@@ -232,7 +232,7 @@ int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec,
     }
     // hpsi[b0 .. b0+bbt) += B_k Q_k[b0 .. b0+bbt) for every k-point
     auto add_bq = [&](int b0, int bbt, hipStream_t s) -> int {
-        const int step = bf ? 1 : kGemmMaxBatch;
+        const int step = bf ? 1 : gemm_nn_batch_limit(P.max_npw);
         for (int k = k0; k < k1; k += step) {
             const KTables &K = P.k[k];
             char *yk = static_cast<char *>(hpsi) + ((size_t)nb * (K.pw_off - P.pw_off[k0]) + (size_t)b0 * K.npw) * ib;

@@ -74,3 +74,24 @@ def test_overlap_keeps_its_batches(ask):
     printf("%d\\n", local_band_batch(P, 0, 0, 1, 128));
     """)
     assert got == [128, 40, 64, 40, 128, 40, 100]
+
+
+def test_batched_products_fit_a_grid(ask):
+    """Several k-points in one launch: their K splits and their column tiles add up in the grid's z and y,
+    which hold 65,536 work-groups each (a 128^3 grid has spheres of up to 2,048,383 plane waves)."""
+    got = ask("""
+    for (int K : {100, 24000, 161235, 1100000, 2048383})
+        for (int M : {1, 500})
+            for (int hint : {0, 16, 64, 1024}) {
+                const int n = gemm_batch_limit(M, 16, K, 16, hint);
+                const int splits = hint ? ceil_div(K, hint) : std::max(512, ceil_div(K, 1024));
+                printf("%d ", n == 1 || (n >= 1 && n <= kGemmMaxBatch && n * splits <= 65536));
+            }
+    for (int G : {100, 24000, 161235, 524000, 1100000, 2048383})
+        printf("%d ", gemm_nn_batch_limit(G));
+    printf("%d %d", gemm_batch_limit(63, 37, 4000, 16, 0), gemm_batch_limit(1, 1, 1100000, 16, 0));
+    """)
+    assert got[:40] == [1] * 40
+    for g, n in zip((100, 24000, 161235, 524000, 1100000, 2048383), got[40:46]):
+        assert 1 <= n <= 8 and n * -(-g // 64) <= 65536
+    assert got[40:44] == [8, 8, 8, 8] and got[46:] == [8, 8]
