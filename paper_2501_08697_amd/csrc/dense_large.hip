@@ -492,6 +492,12 @@ int trd_multi(int n, z64 *A, int ld, double *d, double *e, z64 *tau, z64 *Vr, z6
     return check_launch("hetrd last");
 }
 
+// Partial sums of the back-transformation's products: the Gram matrices of the reflector blocks
+// (kPL x kPL, also where fewer vectors are wanted) and V^H coef (kPL x nw).
+size_t heev_part_bytes(int n, int nw) {
+    return std::max(gemm_cn_part_bytes(kPL, kPL, n, 16, 0), gemm_cn_part_bytes(kPL, nw, n, 16, 0));
+}
+
 // Scratch of the large-order routines (bytes), carved in the order below.
 size_t heev_large_scratch_bytes(int n, int nw) {
     const size_t zn = sizeof(z64);
@@ -502,7 +508,7 @@ size_t heev_large_scratch_bytes(int n, int nw) {
            + (size_t)n * n * sizeof(double)               // Z
            + (size_t)2 * (n + kPL) * kPL * zn             // Gram, T of every block
            + (size_t)2 * nw * kPL * zn                    // S, S'
-           + gemm_cn_part_bytes(kPL, nw, n, 16, 0) + 4096;
+           + heev_part_bytes(n, nw) + 4096;
 }
 
 int stein_vectors(int n, const double *d, const double *e, int nw, const double *w, double *Z, int ldz, void *work,
@@ -530,7 +536,7 @@ int heev_lowest_large(int n, z64 *A, int ld, int nw, double *w, z64 *coef, int l
     z64 *T = reinterpret_cast<z64 *>(take(tri_bytes));
     z64 *S = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)nw * kPL));
     z64 *Sp = reinterpret_cast<z64 *>(take(sizeof(z64) * (size_t)nw * kPL));
-    void *part = take(gemm_cn_part_bytes(kPL, nw, n, 16, 0));
+    void *part = take(heev_part_bytes(n, nw));
     {
         KernelTimer kt("hetrd_mc", st);
         APW_TRY(trd_multi(n, A, ld, d, e, tau, Vr, trd, st));

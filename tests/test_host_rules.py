@@ -13,6 +13,9 @@ PRELUDE = r"""
 #include "local.hpp"
 #include <cstdio>
 using namespace apw;
+namespace apw {
+size_t heev_part_bytes(int n, int nw);   // dense_large.hip
+}
 // the fields of a plan that the rules read: a sphere of a quarter of the grid length
 static void fill(Plan &P, int n1, int n2, int n3) {
     P.N1 = n1; P.N2 = n2; P.N3 = n3;
@@ -95,3 +98,18 @@ def test_batched_products_fit_a_grid(ask):
     for g, n in zip((100, 24000, 161235, 524000, 1100000, 2048383), got[40:46]):
         assert 1 <= n <= 8 and n * -(-g // 64) <= 65536
     assert got[40:44] == [8, 8, 8, 8] and got[46:] == [8, 8]
+
+
+def test_eigensolver_partial_sums_fit(ask):
+    """The region the eigensolver sets aside for partial sums holds those of every product that uses it, also
+    where fewer eigenvectors than a reflector block's 32 are wanted (at one vector of order 300 the Gram matrices
+    of the blocks need 32 times the sums of V^H coef, and ran on into the next region)."""
+    got = ask("""
+    for (int n : {257, 300, 1024, 4096})
+        for (int nw : {1, 20, 31, 32, 33, 200})
+            for (int m : {1, 5, 32})
+                printf("%d ", heev_part_bytes(n, nw) >= gemm_cn_part_bytes(m, m, n, 16, 0) &&
+                                  heev_part_bytes(n, nw) >= gemm_cn_part_bytes(m, nw, n, 16, 0));
+    printf("%d", gemm_cn_part_bytes(32, 1, 300, 16, 0) < gemm_cn_part_bytes(32, 32, 300, 16, 0));
+    """)
+    assert got == [1] * (4 * 6 * 3) + [1]
