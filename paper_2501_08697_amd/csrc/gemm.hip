@@ -59,17 +59,22 @@ constexpr int kGemmWaves = 2;
 // through K together (with the row tiles fastest, a chunk of a 2304 x 1024 product
 // kept all 36 A tiles in flight and read 15.7x the operands).
 // One launch covers up to kMaxBatch products of one shape M x N (the k-points of a call, whose
-// K = npw differ): grid z counts their splits one after the other.
+// K = npw differ): grid z counts their splits one after the other. A batch has room for NB, 1 or
+// kMaxBatch, and keeps a product's fields together: what a launch looks up in its arguments it waits
+// for before its first load. MIXED_FP32 H psi of 32 projectors x 16 bands at 32^3 (one product a launch)
+// took 60.9 us with eight arrays of fields and a search in every launch, 59.0 so.
 // herm: A and B are the same rows, so the result is Hermitian; tiles with i0 > j0 are left out
 // and k_reduce fills them in from their mirror images (36 of 64 tiles at 512 x 512: the Gram
 // matrix of 512 bands of 115k plane waves takes 2.05 ms, whole it took 2.95).
-struct CnBatch {
+template <int NB> struct CnBatch {
     int n;
-    int K[kMaxBatch], kchunk[kMaxBatch], z0[kMaxBatch + 1];   // z0[p]: first split of product p in grid z
-    int64_t lda[kMaxBatch], ldb[kMaxBatch], a[kMaxBatch], b[kMaxBatch];   // rows and element offsets of A and B
+    struct {
+        int K, kchunk, z0;         // z0: first split in grid z
+        int64_t lda, ldb, a, b;    // rows and element offsets of A and B
+    } p[NB];
 };
-template <typename T, typename TS = T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_cn_part(int M, int N, CnBatch bt, const cx<TS> *__restrict__ A,
+template <typename T, typename TS, int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_cn_part(int M, int N, CnBatch<NB> bt, const cx<TS> *__restrict__ A,
                                                       const cx<TS> *__restrict__ B, cx<T> *__restrict__ part, int gm, int herm) {
     __shared__ cx<T> As[TM][KP];
     __shared__ cx<T> Bs[TN][KP];
@@ -83,12 +88,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     const int i0 = (first + r % rows) * TM, j0 = (r / rows) * TN;
     if (herm && i0 > j0) return;
     int pb = 0;
-    while (pb + 1 < bt.n && bz >= bt.z0[pb + 1]) ++pb;
+    if constexpr (NB > 1)
+        while (pb + 1 < bt.n && bz >= bt.p[pb + 1].z0) ++pb;
     const int s = bz;   // the partial sums of the products follow each other
-    const int kb = (bz - bt.z0[pb]) * bt.kchunk[pb], ke = min(bt.K[pb], kb + bt.kchunk[pb]);
-    const int64_t lda = bt.lda[pb], ldb = bt.ldb[pb];
-    A += bt.a[pb];
-    B += bt.b[pb];
+    const auto &pr = bt.p[pb];
+    const int kb = (bz - pr.z0) * pr.kchunk, ke = min(pr.K, kb + pr.kchunk);
+    const int64_t lda = pr.lda, ldb = pr.ldb;
+    A += pr.a;
+    B += pr.b;
     using AV = typename Acc<T>::V;
     AV c1[2][2], c2[2][2], c3[2][2];   // sums of ar br, ai bi, (ar - ai)(br + bi)
 #pragma unroll
@@ -324,13 +331,15 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, RedBatch r
 // npw differ): grid y counts their column tiles one after the other.
 // tri: A is lower triangular (zeros stored above its diagonal), so a row tile stops at its own
 // last column (a 512 x 512 inverse factor on 512 bands of 115k plane waves: 2.2 ms, whole 3.0).
-struct NnBatch {
+template <int NB> struct NnBatch {
     int n;
-    int G[kMaxBatch], y0[kMaxBatch + 1];   // y0[p]: first column tile of product p in grid y
-    int64_t ldb[kMaxBatch], ldc[kMaxBatch], a[kMaxBatch], b[kMaxBatch], c[kMaxBatch];   // rows, element offsets
+    struct {
+        int G, y0;                    // y0: first column tile in grid y
+        int64_t ldb, ldc, a, b, c;    // rows, element offsets
+    } p[NB];
 };
-template <typename T, typename TC, typename TS = T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_nn(int M, int Kall, NnBatch bt, const cx<TS> *__restrict__ A, int64_t lda,
+template <typename T, typename TC, typename TS, int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves))) void k_gemm_nn(int M, int Kall, NnBatch<NB> bt, const cx<TS> *__restrict__ A, int64_t lda,
                                                  const cx<TS> *__restrict__ B, cx<TC> *__restrict__ C, double alpha, double beta, int tri) {
     __shared__ cx<T> As[TM][KP];
     __shared__ cx<T> Bs[KT][TN + 1];
@@ -338,13 +347,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     int bx, by, bz;
     xcd_block(bx, by, bz);   // the row tiles of one column block share an L2
     int pb = 0;
-    while (pb + 1 < bt.n && by >= bt.y0[pb + 1]) ++pb;
-    const int j0 = bx * TM, g0 = (by - bt.y0[pb]) * TN, G = bt.G[pb];
+    if constexpr (NB > 1)
+        while (pb + 1 < bt.n && by >= bt.p[pb + 1].y0) ++pb;
+    const auto &pr = bt.p[pb];
+    const int j0 = bx * TM, g0 = (by - pr.y0) * TN, G = pr.G;
     const int K = tri ? min(Kall, j0 + TM) : Kall;
-    const int64_t ldb = bt.ldb[pb], ldc = bt.ldc[pb];
-    A += bt.a[pb];
-    B += bt.b[pb];
-    C += bt.c[pb];
+    const int64_t ldb = pr.ldb, ldc = pr.ldc;
+    A += pr.a;
+    B += pr.b;
+    C += pr.c;
     using AV = typename Acc<T>::V;
     AV c1[2][2], c2[2][2], c3[2][2];   // sums of ar br, ai bi, (ar + ai)(br + bi)
 #pragma unroll
@@ -622,31 +633,34 @@ int gemm_batch_limit(int M, int N, int K, int elem_bytes, int chunk_hint) {
 }
 int gemm_nn_batch_limit(int G) { return std::max(1, std::min(kMaxBatch, kMaxGridYZ / ceil_div(G, TN))); }
 
-template <typename T, typename TS = T>
-static int cn_part(int M, int N, const CnProduct *pr, int np, const void *A, const void *B, void *part,
-                   int chunk_hint, bool wide, RedBatch *rb, hipStream_t st, int herm = 0) {
-    CnBatch bt;
+template <typename T, typename TS, int NB>
+static int cn_part_nb(int M, int N, const CnProduct *pr, int np, const void *A, const void *B, void *part,
+                      int chunk_hint, bool wide, RedBatch *rb, hipStream_t st, int herm) {
+    CnBatch<NB> bt;
     bt.n = np;
-    bt.z0[0] = 0;
+    rb->z0[0] = 0;
     for (int i = 0; i < np; ++i) {
-        bt.K[i] = pr[i].K;
-        bt.z0[i + 1] = bt.z0[i] + splits_for(M, N, pr[i].K, chunk_hint, np, wide, &bt.kchunk[i]);
-        bt.lda[i] = pr[i].lda;
-        bt.ldb[i] = pr[i].ldb;
-        bt.a[i] = pr[i].a;
-        bt.b[i] = pr[i].b;
+        auto &p = bt.p[i];
+        p = {pr[i].K, 0, rb->z0[i], pr[i].lda, pr[i].ldb, pr[i].a, pr[i].b};
+        rb->z0[i + 1] = p.z0 + splits_for(M, N, p.K, chunk_hint, np, wide, &p.kchunk);
     }
-    for (int i = 0; i <= np; ++i) rb->z0[i] = bt.z0[i];
-    dim3 grid(ceil_div(M, TM), ceil_div(N, TN), bt.z0[np]);
+    dim3 grid(ceil_div(M, TM), ceil_div(N, TN), rb->z0[np]);
     // group of row tiles: about one XCD's resident work-groups (32 CUs x 3) per group;
     // a chunk of at most two such groups keeps the row tiles fastest (one group): at
     // 864 x 512 per k-point that order measured 1-2% faster than groups of 12 rows
     const int tiles = (int)(grid.x * grid.y);
     const int gm = tiles <= 192 ? (int)grid.x : std::max(1, std::min((int)grid.x, 96 / (int)grid.y));
     KernelTimer kt("gemm_cn", st);
-    hipLaunchKernelGGL((k_gemm_cn_part<T, TS>), grid, dim3(256), 0, st, M, N, bt, static_cast<const cx<TS> *>(A),
+    hipLaunchKernelGGL((k_gemm_cn_part<T, TS, NB>), grid, dim3(256), 0, st, M, N, bt, static_cast<const cx<TS> *>(A),
                        static_cast<const cx<TS> *>(B), static_cast<cx<T> *>(part), gm, herm);
     return check_launch("gemm_cn");
+}
+
+template <typename T, typename TS = T>
+static int cn_part(int M, int N, const CnProduct *pr, int np, const void *A, const void *B, void *part,
+                   int chunk_hint, bool wide, RedBatch *rb, hipStream_t st, int herm = 0) {
+    return np > 1 ? cn_part_nb<T, TS, kMaxBatch>(M, N, pr, np, A, B, part, chunk_hint, wide, rb, st, herm)
+                  : cn_part_nb<T, TS, 1>(M, N, pr, np, A, B, part, chunk_hint, wide, rb, st, herm);
 }
 
 // T: arithmetic and partial sums; TS: storage of A, B and C.
@@ -718,28 +732,30 @@ int proj_dapply(int prec, int M, int N, const CnProduct *pr, int np, const void 
                                             st);
 }
 
+template <typename T, typename TC, typename TS, int NB>
+static int gemm_nn_nb(int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B, void *C,
+                      double alpha, double beta, hipStream_t st, int tri) {
+    if (M <= 0) return ABACUS_PW_OK;
+    NnBatch<NB> bt;
+    bt.n = np;
+    int tiles = 0;
+    for (int i = 0; i < np; ++i) {
+        bt.p[i] = {pr[i].G, tiles, pr[i].ldb, pr[i].ldc, pr[i].a, pr[i].b, pr[i].c};
+        tiles += ceil_div(pr[i].G, TN);
+    }
+    if (tiles == 0) return ABACUS_PW_OK;
+    dim3 grid(ceil_div(M, TM), tiles);
+    KernelTimer kt("gemm_nn", st);
+    hipLaunchKernelGGL((k_gemm_nn<T, TC, TS, NB>), grid, dim3(256), 0, st, M, K, bt, static_cast<const cx<TS> *>(A), lda,
+                       static_cast<const cx<TS> *>(B), static_cast<cx<TC> *>(C), alpha, beta, tri);
+    return check_launch("gemm_nn");
+}
+
 template <typename T, typename TC, typename TS = T>
 static int gemm_nn_batch_t(int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
                            void *C, double alpha, double beta, hipStream_t st, int tri = 0) {
-    if (M <= 0) return ABACUS_PW_OK;
-    NnBatch bt;
-    bt.n = np;
-    bt.y0[0] = 0;
-    for (int i = 0; i < np; ++i) {
-        bt.G[i] = pr[i].G;
-        bt.y0[i + 1] = bt.y0[i] + ceil_div(pr[i].G, TN);
-        bt.ldb[i] = pr[i].ldb;
-        bt.ldc[i] = pr[i].ldc;
-        bt.a[i] = pr[i].a;
-        bt.b[i] = pr[i].b;
-        bt.c[i] = pr[i].c;
-    }
-    if (bt.y0[np] == 0) return ABACUS_PW_OK;
-    dim3 grid(ceil_div(M, TM), bt.y0[np]);
-    KernelTimer kt("gemm_nn", st);
-    hipLaunchKernelGGL((k_gemm_nn<T, TC, TS>), grid, dim3(256), 0, st, M, K, bt, static_cast<const cx<TS> *>(A), lda,
-                       static_cast<const cx<TS> *>(B), static_cast<cx<TC> *>(C), alpha, beta, tri);
-    return check_launch("gemm_nn");
+    return np > 1 ? gemm_nn_nb<T, TC, TS, kMaxBatch>(M, K, pr, np, A, lda, B, C, alpha, beta, st, tri)
+                  : gemm_nn_nb<T, TC, TS, 1>(M, K, pr, np, A, lda, B, C, alpha, beta, st, tri);
 }
 
 int gemm_nn_batch(int prec, int M, int K, const NnProduct *pr, int np, const void *A, int64_t lda, const void *B,
