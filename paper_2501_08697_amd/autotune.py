@@ -5,8 +5,8 @@ precision by coordinate descent: starting from the defaults, each knob in turn
 is swept over its candidate values with the others fixed, keeping the fastest;
 two sweeps. Each candidate is timed with HIP events as the best of three
 repetitions of `reps` H psi calls, after one warm-up call. The winner is cached in a JSON file keyed by the
-problem's shape (grid, sphere sizes, projectors, bands, precision); the cache
-path is ABACUS_PW_AUTOTUNE_CACHE or ~/.cache/abacus_pw/autotune.json.
+meaning of the knobs (KNOBS) and the problem's shape (grid, spheres, projectors, bands,
+precision); the cache path is ABACUS_PW_AUTOTUNE_CACHE or ~/.cache/abacus_pw/autotune.json.
 
 The knobs change launch shapes, work-group band counts and whether the
 projector GEMMs run on a second stream beside the local term; the split-K
@@ -17,8 +17,15 @@ from __future__ import annotations
 
 import json
 import os
+import zlib
+
+import numpy as np
 
 from . import binding as B
+
+# Version of what the knobs select; entries of another are not used. 2: yz_mode 0 runs the column
+# passes where they fit, yz_bands and x_bands also size their work-groups.
+KNOBS = 2
 
 CANDIDATES = {
     "yz_mode": [1, 2],
@@ -39,7 +46,9 @@ def cache_path() -> str:
 
 
 def key(dp: B.DeviceProblem, nb: int, precision: int) -> str:
-    return f"fft={dp.fft};npw={list(map(int, dp.npw))};nproj={dp.nproj};nb={nb};prec={precision}"
+    sphere = zlib.crc32(np.ascontiguousarray(dp.prob.miller, dtype=np.int32))
+    return (f"knobs={KNOBS};fft={dp.fft};npw={list(map(int, dp.npw))};sphere={sphere:08x};nproj={dp.nproj};nb={nb};"
+            f"prec={precision}")
 
 
 def _apply(cfg):
