@@ -8,25 +8,29 @@ namespace apw {
 // The x transform runs one task per thread and phase (C max(A1, B1) <= threads), the y
 // transform's tasks wrap around. C is the widest divisor of N2 that the threads and LDS allow:
 // at 120^3 30 columns took 44.9 ms of plane passes per call of 4,096 bands, 24 took 48.1 and
-// 20 took 55 (shorter chunks leave threads without a task in F).
+// 20 took 55 (shorter chunks leave threads without a task in F). A plane alone on its CU takes 512
+// threads: H psi of 128 bands and one atom at 90^3 with 49 slab rows took 1148 us with 256 (1122
+// through the slab passes), 946 so.
 PlaneShape plane_shape(const Plan &P, int fft_prec) {
     PlaneShape s{0, 0, P.N2 | 1, 0};
     int a1, b1, a2, b2;
     if (!lds_split_host(P.N1, &a1, &b1) || !lds_split_host(P.N2, &a2, &b2)) return s;
     if (P.N1 != P.N2 && !(P.zero_band[0] && P.zero_band[1])) return s;
-    const int m1 = std::max(a1, b1), m2 = std::max(a2, b2), nt = plane_threads(P.N1, P.N2);
+    const int m1 = std::max(a1, b1), m2 = std::max(a2, b2);
     auto lds = [&](int C) {
         return ((size_t)P.nslab * s.ldr + (size_t)(P.N1 - P.nslab) * C + P.N1 + P.N2 + 1) *
                (fft_prec == 0 ? sizeof(z64) : sizeof(c32));
     };
-    for (int C = std::min(P.N2, nt / m1); C >= 1; --C)
-        if (P.N2 % C == 0 && lds(C) <= 160 * 1024) {
-            s.C = C;
-            break;
-        }
-    if (s.C == 0) return s;
-    s.lds = lds(s.C);
-    s.NT = std::min(nt, (std::max(s.C * m1, P.nslab * m2) + 63) / 64 * 64);
+    auto fit = [&](int nt) {
+        s.C = std::min(P.N2, nt / m1);
+        while (s.C > 0 && (P.N2 % s.C != 0 || lds(s.C) > 160 * 1024)) --s.C;
+        s.lds = s.C > 0 ? lds(s.C) : 0;
+        s.NT = std::min(nt, (std::max(s.C * m1, P.nslab * m2) + 63) / 64 * 64);
+    };
+    fit(plane_threads(P.N1, P.N2));
+    // a plane with more slab rows than usual may be alone on its CU all the same: 256 threads would
+    // then be half of what the CU holds
+    if (s.lds > 80 * 1024) fit(512);
     return s;
 }
 

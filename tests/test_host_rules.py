@@ -113,3 +113,19 @@ def test_eigensolver_partial_sums_fit(ask):
     printf("%d", gemm_cn_part_bytes(32, 1, 300, 16, 0) < gemm_cn_part_bytes(32, 32, 300, 16, 0));
     """)
     assert got == [1] * (4 * 6 * 3) + [1]
+
+
+def test_a_plane_alone_on_its_cu_takes_all_its_threads(ask):
+    """Threads and LDS (KB) of a plane work-group: two of 256 threads to a CU, or one of 512, never one of 256."""
+    got = ask("""
+    for (int n : {45, 64, 72, 80, 81, 90, 96, 108})
+        for (int rows : {n / 2 + 1, n / 2 + 5, 2 * n / 3, 4 * n / 5}) {
+            Plan P;
+            fill(P, n, n, n);
+            P.nslab = rows;
+            const PlaneShape s = plane_shape(P, 0);
+            printf("%d %d %d ", s.C, s.NT, (int)(s.lds / 1024));
+        }
+    """)
+    for c, nt, kb in zip(got[::3], got[1::3], got[2::3]):
+        assert c == 0 or (kb < 160 and nt <= 512 and (nt > 256 if kb >= 80 else nt <= 512)), (c, nt, kb)
