@@ -8,20 +8,36 @@
 
 namespace apw {
 
-// Bands per plane work-group. A work-group's tables cost about as much as 0.6 bands (measured
-// at 72^3: 250, 254 and 275 us with 4, 2 and 8), and the last round of work-groups may be
-// part empty: the fewest rounds times bands, tables included.
-inline int plane_bands(int n3, int nvb, int slots) {
+// Bands per plane work-group, of which per_cu fit on a compute unit. A round of work-groups takes
+// the longer the more of them share a unit, 1 + (q - 1) / 2 for q, and the last round may be part
+// empty; a work-group's tables cost about as much as 0.2 bands. Fitted to 153 cases of length and
+// bands, 1 to 8 bands a work-group each: within 0.6% of the best on average, 7.4% at most (2, 4 or 8
+// bands by rounds alone, two work-groups of 256 to a unit whatever the registers allow: 7.3% and
+// 47%). FP32 at 72^3 x 48 bands 89 -> 71 us, FP64 x 16 bands 65 -> 48.
+inline int plane_bands(int n3, int nvb, int per_cu) {
+    auto round = [](int q) { return 0.5 * (q + 1); };
+    const int slots = 256 * per_cu;
     int best = 1;
     double cost = 1e30;
-    for (int b = 8; b >= 1; b /= 2) {
-        const double t = ceil_div(n3 * ceil_div(nvb, b), slots) * (std::min(b, nvb) + 0.6);
-        if (t < cost) {
+    for (int b = 1; b <= std::min(8, nvb); ++b) {
+        const int wgs = n3 * ceil_div(nvb, b), last = wgs % slots;
+        const double t = (b + 0.2) * (wgs / slots * round(per_cu) + (last > 0 ? round(ceil_div(last, 256)) : 0.0));
+        if (t < 0.9999 * cost) {
             cost = t;
             best = b;
         }
     }
-    return std::min(best, nvb);
+    return best;
+}
+
+// Wavefronts per SIMD that a kernel's registers allow.
+template <typename K> int kernel_waves(K kernel) {
+    int groups = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&groups, kernel, 64, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 2;
+    }
+    return std::max(2, groups / 4);
 }
 
 template <int N1, int N2, bool ZB, typename T = double> static int launch_plane(const ColumnsCall &c) {
@@ -36,8 +52,9 @@ template <int N1, int N2, bool ZB, typename T = double> static int launch_plane(
         once = true;
     }
     const int nvb = c.nkb * c.ba.bbt;
-    const int per_cu = std::max(1, std::min((int)(160 * 1024 / sh.lds), 512 / sh.NT));
-    const int bpw = std::min(nvb, g_x_bands > 0 ? g_x_bands : plane_bands(P.N3, nvb, 256 * per_cu));
+    static const int waves = kernel_waves(kernel);
+    const int per_cu = std::max(1, std::min((int)(160 * 1024 / sh.lds), waves * 256 / sh.NT));
+    const int bpw = std::min(nvb, g_x_bands > 0 ? g_x_bands : plane_bands(P.N3, nvb, per_cu));
     const int ngrp = ceil_div(nvb, bpw);
     const void *const *tw = prec == 0 ? P.tw64 : P.tw32;
     PlaneArgs a{P.kdesc + c.k0, c.vt, tw[0], tw[1], P.xrow, P.nslab, P.ldc, sh.ldr, P.N3, nvb, c.ba.bbt, bpw,
