@@ -34,6 +34,20 @@ PlaneShape plane_shape(const Plan &P, int fft_prec) {
     return s;
 }
 
+// Whether the columns move and transform less than the slab passes would. Their share of the slab is
+// pi / 2 times the sphere's radius over the grid length, 0.41 on the usual grid; small planes gain
+// at any share, and so do planes that the slab passes cannot hold whole in LDS. H psi of 48 bands
+// against the slab passes, FP64: share 0.68 72^3 440 / 480 us, 80^3 625 / 697, 96^3 1092 / 1223;
+// 0.58 72^3 353 / 308, but where the plane is alone on its CU 81^3 491 / 503, 96^3 810 / 866; 0.51
+// 81^3 405 / 347, 96^3 658 / 623. FP32: 0.51 64^3 234 / 222 (100 bands), 72^3 293 / 299, 80^3 429 / 477; 0.46
+// 72^3 273 / 260, 80^3 371 / 346.
+bool columns_pay(const Plan &P, int fft_prec) {
+    const size_t eb = fft_prec == 0 ? sizeof(z64) : sizeof(c32);
+    if (P.N1 * P.N2 < 72 * 72 || (size_t)P.N2 * P.N3 * eb > 160 * 1024) return true;
+    const int most = fft_prec == 1 ? 48 : plane_shape(P, 0).lds > 80 * 1024 ? 55 : 62;   // per cent
+    return 100 * (int64_t)P.max_ncol <= (int64_t)most * P.nslab * P.N2;
+}
+
 // Bands per z-pass work-group: up to 4 share the tables read once, while the launch keeps
 // 2048 work-groups (eight a CU).
 static int z_bands(const ColumnsCall &c, int ngrp) {

@@ -332,7 +332,7 @@ void k_plane(cx<T> *__restrict__ col, PlaneArgs p) {
 #pragma unroll
     for (int q = 0; q < A1; ++q) fo[q] = p.xrow[min(g, B1 - 1) + B1 * q];
     // the task's twiddles, in registers where there is room for them
-        constexpr bool kTwReg = N1 <= 120;
+    constexpr bool kTwReg = N1 <= 120;
     cx<T> tx[kTwReg ? B1 : 1];
     if constexpr (kTwReg) {
 #pragma unroll
@@ -588,6 +588,7 @@ struct PlaneShape {
     size_t lds;
 };
 PlaneShape plane_shape(const Plan &P, int fft_prec);
+bool columns_pay(const Plan &P, int fft_prec);
 
 int columns_inverse(const ColumnsCall &c, const void *psi, const double *v);
 int columns_plane(const ColumnsCall &c);

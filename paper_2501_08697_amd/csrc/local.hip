@@ -1201,7 +1201,8 @@ int local_sum_parts(const Plan &P, const double *part, int G, double scale, doub
 }
 
 // Whether the call's planes run through the column passes (columns.hpp): FP64 in the automatic
-// plane mode, a plane that fits in LDS, and a kernel for the pair of lengths. They took the
+// plane mode, a plane that fits in LDS, a kernel for the pair of lengths, and spheres narrow enough
+// (columns_pay). They took the
 // FP64 local term at 72^3 (128 bands) from 461 to 345 us, at 120^3 (4,096 bands) from 78.9 to
 // 58.6 ms. In FP32 the plane pass is bound by VALU instructions, which are as many as in FP64:
 // H psi with two atoms took 47.5 us against 56.2 through the slab passes at 32^3 x 64 bands, 84.9
@@ -1212,7 +1213,7 @@ int local_sum_parts(const Plan &P, const double *part, int G, double scale, doub
 // FP32 roundings (2e-9 of H psi) that those results would show.
 bool local_uses_columns(const Plan &P, int fft_prec, int io_prec) {
     if (fft_prec == 1 && (io_prec == 0 || P.N1 != P.N2 || P.N1 >= kColumnsF32 || P.N3 >= kColumnsF32)) return false;
-    return g_yz_mode == 0 && plane_shape(P, fft_prec).C > 0;
+    return g_yz_mode == 0 && plane_shape(P, fft_prec).C > 0 && columns_pay(P, fft_prec);
 }
 
 static size_t column_bytes(const Plan &P, int fft_prec) {

@@ -139,3 +139,16 @@ def test_bands_of_a_plane_work_group(ask):
     got = ask("".join(f'printf("%d ", plane_bands({n}, {nb}, {q}));' for n, nb, q in good))
     for g, (case, ok) in zip(got, good.items()):
         assert g in ok, (case, g)
+
+
+def test_columns_of_wide_spheres(ask):
+    """Which spheres take the column passes, by their columns' share of the slab (per cent): planes from 72 x 72
+    on, of those that the slab passes hold whole in LDS, only up to a share at which they are not slower. (At 108 and 68 the plane does not fit.)"""
+    def uses(n, prec, share):
+        return f"""{{ Plan P; fill(P, {n}, {n}, {n}); P.nslab = (int)({n} * {share} / 78.5) | 1;
+                    P.max_ncol = {share} * P.nslab * {n} / 100; P.ldc = (P.max_ncol + 15) / 16 * 16;
+                    printf("%d ", (int)local_uses_columns(P, {prec}, {prec})); }}"""
+    table = {(72, 0): (1, 1, 1, 0), (81, 0): (1, 1, 0, 0), (96, 0): (1, 1, 0, 0), (108, 0): (1, 1, 1, 0),
+             (48, 0): (1, 1, 1, 1), (72, 1): (1, 0, 0, 0), (80, 1): (1, 0, 0, 0), (64, 1): (1, 1, 1, 1)}
+    got = ask("".join(uses(n, prec, share) for n, prec in table for share in (41, 51, 58, 68)))
+    assert [tuple(got[i:i + 4]) for i in range(0, len(got), 4)] == list(table.values())
