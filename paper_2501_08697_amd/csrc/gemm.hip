@@ -67,9 +67,9 @@ constexpr int kGemmWaves = 2;
 // and k_reduce fills them in from their mirror images (36 of 64 tiles at 512 x 512: the Gram
 // matrix of 512 bands of 115k plane waves takes 2.05 ms, whole it took 2.95).
 template <int NB> struct CnBatch {
-    int n;
+    int n, z0[NB];                 // z0: first splits in grid z
     struct {
-        int K, kchunk, z0;         // z0: first split in grid z
+        int K, kchunk;
         int64_t lda, ldb, a, b;    // rows and element offsets of A and B
     } p[NB];
 };
@@ -89,10 +89,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     if (herm && i0 > j0) return;
     int pb = 0;
     if constexpr (NB > 1)
-        while (pb + 1 < bt.n && bz >= bt.p[pb + 1].z0) ++pb;
+        while (pb + 1 < bt.n && bz >= bt.z0[pb + 1]) ++pb;
     const int s = bz;   // the partial sums of the products follow each other
     const auto &pr = bt.p[pb];
-    const int kb = (bz - pr.z0) * pr.kchunk, ke = min(pr.K, kb + pr.kchunk);
+    const int kb = (bz - bt.z0[pb]) * pr.kchunk, ke = min(pr.K, kb + pr.kchunk);
     const int64_t lda = pr.lda, ldb = pr.ldb;
     A += pr.a;
     B += pr.b;
@@ -332,9 +332,9 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_dapply(int M, RedBatch r
 // tri: A is lower triangular (zeros stored above its diagonal), so a row tile stops at its own
 // last column (a 512 x 512 inverse factor on 512 bands of 115k plane waves: 2.2 ms, whole 3.0).
 template <int NB> struct NnBatch {
-    int n;
+    int n, y0[NB];                    // y0: first column tiles in grid y
     struct {
-        int G, y0;                    // y0: first column tile in grid y
+        int G;
         int64_t ldb, ldc, a, b, c;    // rows, element offsets
     } p[NB];
 };
@@ -348,9 +348,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGemmWaves)
     xcd_block(bx, by, bz);   // the row tiles of one column block share an L2
     int pb = 0;
     if constexpr (NB > 1)
-        while (pb + 1 < bt.n && by >= bt.p[pb + 1].y0) ++pb;
+        while (pb + 1 < bt.n && by >= bt.y0[pb + 1]) ++pb;
     const auto &pr = bt.p[pb];
-    const int j0 = bx * TM, g0 = (by - pr.y0) * TN, G = pr.G;
+    const int j0 = bx * TM, g0 = (by - bt.y0[pb]) * TN, G = pr.G;
     const int K = tri ? min(Kall, j0 + TM) : Kall;
     const int64_t ldb = pr.ldb, ldc = pr.ldc;
     A += pr.a;
@@ -641,8 +641,9 @@ static int cn_part_nb(int M, int N, const CnProduct *pr, int np, const void *A, 
     rb->z0[0] = 0;
     for (int i = 0; i < np; ++i) {
         auto &p = bt.p[i];
-        p = {pr[i].K, 0, rb->z0[i], pr[i].lda, pr[i].ldb, pr[i].a, pr[i].b};
-        rb->z0[i + 1] = p.z0 + splits_for(M, N, p.K, chunk_hint, np, wide, &p.kchunk);
+        p = {pr[i].K, 0, pr[i].lda, pr[i].ldb, pr[i].a, pr[i].b};
+        bt.z0[i] = rb->z0[i];
+        rb->z0[i + 1] = rb->z0[i] + splits_for(M, N, p.K, chunk_hint, np, wide, &p.kchunk);
     }
     dim3 grid(ceil_div(M, TM), ceil_div(N, TN), rb->z0[np]);
     // group of row tiles: about one XCD's resident work-groups (32 CUs x 3) per group;
@@ -740,7 +741,8 @@ static int gemm_nn_nb(int M, int K, const NnProduct *pr, int np, const void *A, 
     bt.n = np;
     int tiles = 0;
     for (int i = 0; i < np; ++i) {
-        bt.p[i] = {pr[i].G, tiles, pr[i].ldb, pr[i].ldc, pr[i].a, pr[i].b, pr[i].c};
+        bt.y0[i] = tiles;
+        bt.p[i] = {pr[i].G, pr[i].ldb, pr[i].ldc, pr[i].a, pr[i].b, pr[i].c};
         tiles += ceil_div(pr[i].G, TN);
     }
     if (tiles == 0) return ABACUS_PW_OK;
