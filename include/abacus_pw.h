@@ -156,10 +156,10 @@ int abacus_pw_apply_h(const abacus_pw_problem *p, int precision, int nb, const v
  * abacus_pw_workspace_size builds the problem's plan if it does not exist (it
  * allocates the plan's tables and its reduced-precision operator copies for
  * `precision`, and synchronises) and writes to *bytes the work-space size
- * abacus_pw_apply_h_ws needs for nb bands at that precision: the slab of
- * grid planes of one band batch at every k-point, the projections and their
+ * abacus_pw_apply_h_ws needs for nb bands at that precision: the grid planes or
+ * z columns of one band batch at every k-point, the projections and their
  * split-K partial sums (and the bf16 / FP32 staging of the mixed modes). The
- * size depends on the tuning knobs (band batch, split-K chunk): query it again
+ * size depends on the tuning knobs (band batch, plane mode, overlap, split-K chunk): query it again
  * after abacus_pw_set_tuning.
  *
  * abacus_pw_apply_h_ws then applies H using `workspace` (device memory of at
@@ -408,11 +408,12 @@ int abacus_pw_profile_read(char *buf, int size);
  * splitk_chunk K chunk of the split-K projection GEMM (multiple of 16)
  * yz_bands     bands handled by one y-z plane (or z column) work-group
  * x_bands      bands handled by one x-pass (or x-y plane) work-group
- * yz_mode      plane kernels: 0 automatic (FP64 H psi: z columns between the passes and the x and
- *              y transforms of a plane in one, where the plane fits in LDS; else y-z planes, whole
- *              in LDS when they fit), 1 whole y-z planes, 2 compact y-z planes (only the plane's
- *              z-column rows in LDS, y transforms in j3 chunks); planes that do not fit whole
- *              always use the compact form
+ * yz_mode      plane kernels: 0 automatic (z columns between the passes and the x and y transforms
+ *              of a plane in one, for FP64 H psi and density where the plane fits in LDS and the
+ *              spheres are not much wider than a quarter of the grid, and for FP32 H psi on cubic
+ *              grids below 90; else y-z planes, whole in LDS when they fit), 1 whole y-z planes, 2
+ *              compact y-z planes (only the plane's z-column rows in LDS, y transforms in j3
+ *              chunks); planes that do not fit whole always use the compact form
  * overlap      0 default (2), 1 the projector GEMMs run on a second stream of the library
  *              (default priority) beside the local term: the projections from the start,
  *              each band batch's B Q as soon as its local term is done; events order the

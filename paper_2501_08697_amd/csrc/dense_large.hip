@@ -275,7 +275,8 @@ __global__ __launch_bounds__(NT) void k_trd_step(TrdArgs a, int k0) {
 }
 
 // Trailing update after a panel of bw columns, A[i][j] -= sum_q V_iq conj(W_jq) + W_iq conj(V_jq)
-// for i, j >= t0 = k0 + bw (full storage; entries (i, j) and (j, i) come out exactly conjugate).
+// for i, j >= t0 = k0 + bw (full storage; entries (i, j) and (j, i) come out conjugate to rounding:
+// which product of a pair is fused into its sum differs).
 // The last w of the panel is finished here, by every work-group for its own rows and columns.
 // A work-group takes 32 rows x 64 columns; a thread one column and eight rows.
 __global__ __launch_bounds__(256) void k_trd_update(TrdArgs a, int k0, int bw) {

@@ -107,17 +107,9 @@ int order(hipEvent_t e, hipStream_t from, hipStream_t to) {
 
 }  // namespace
 
-// H psi for nb bands at the k-points [k0, k1): psi and hpsi start at k0's [nb][npw_k] block.
-// The local term runs every k-point of a band batch in one launch per pass and
-// writes hpsi = (T + V) psi; the projector GEMMs run per k-point: the
-// projections Q_k = D B_k^H psi_k, then hpsi += B_k Q_k. With the overlap knob on
-// the projections start on the side stream at once and each band batch's B Q
-// follows there as soon as that batch's local term is done, so the GEMMs share
-// the GPU with the plane passes. Off by default: on the 72^3 / 23847-PW case the
-// concurrent kernels slow each other down about as much as they overlap.
-// The projector GEMMs of several k-points share a launch (as many as keep the partial sums
-// bounded): 7 atoms x 9 projectors, 37 bands at three k-points ran three launches of 35 to
-// 138 work-groups each. MIXED_FP32 stages one k-point's psi at a time.
+// k-points whose projections share a launch (as many as keep the partial sums bounded): 7 atoms x 9
+// projectors, 37 bands at three k-points ran three launches of 35 to 138 work-groups each. MIXED_FP32
+// and MIXED_BF16 stage one k-point's psi at a time, so they go one by one.
 static int proj_batch(const Plan &P, int prec, int nb, int k0, int k1) {
     if (prec == ABACUS_PW_MIXED_FP32 || prec == ABACUS_PW_MIXED_BF16) return 1;
     return std::min(k1 - k0, gemm_batch_limit(P.nproj, nb, P.max_npw, prec == ABACUS_PW_FP64 ? 16 : 8, g_splitk_chunk));
@@ -149,6 +141,15 @@ size_t hwork_total(const size_t sz[kHWorkParts]) {
     return t;
 }
 
+// H psi for nb bands at the k-points [k0, k1): psi and hpsi start at k0's [nb][npw_k] block.
+// The local term runs every k-point of a band batch in one launch per pass and
+// writes hpsi = (T + V) psi; the projector GEMMs form the projections Q_k = D B_k^H psi_k,
+// then hpsi += B_k Q_k, of up to eight k-points a launch (projections in the mixed modes and
+// MIXED_BF16 one k-point a launch). With the overlap knob on
+// the projections start on the side stream at once and each band batch's B Q
+// follows there as soon as that batch's local term is done, so the GEMMs share
+// the GPU with the plane passes. Off by default: on the 72^3 / 23847-PW case the
+// concurrent kernels slow each other down about as much as they overlap.
 int apply_h_range(const abacus_pw_problem &p, Plan &P, int k0, int k1, int prec, int nb, const void *psi, void *hpsi,
                   hipStream_t st, bool refresh_copies, void *ext_ws, size_t ext_bytes, void *proj) {
     const bool bf = prec == ABACUS_PW_MIXED_BF16;

@@ -1204,11 +1204,12 @@ int local_sum_parts(const Plan &P, const double *part, int G, double scale, doub
 // plane mode, a plane that fits in LDS, a kernel for the pair of lengths, and spheres narrow enough
 // (columns_pay). They took the
 // FP64 local term at 72^3 (128 bands) from 461 to 345 us, at 120^3 (4,096 bands) from 78.9 to
-// 58.6 ms. In FP32 the plane pass is bound by VALU instructions, which are as many as in FP64:
-// H psi with two atoms took 47.5 us against 56.2 through the slab passes at 32^3 x 64 bands, 84.9
-// against 127 at 48^3 x 96, 251 against 268 at 72^3 x 128 and 356 against 386 at 81^3 x 128, but 1151
-// against 1106 at 90^3 x 256, and the local term 16.2 against 13.9 ms at 128^3. So FP32 takes the
-// column passes on equal x and y lengths below kColumnsF32. The mixed modes, whose results are
+// 58.6 ms. FP32 gains less: H psi of 100 bands with one atom, sphere radius N / 3.8, took 121 us against
+// 168 through the slab passes at 54^3, 162 against 191 at 64^3, 225 against 236 at 72^3 and 289 against
+// 356 at 81^3; at 90^3 x 256 it had taken 1151 against 1106 and the local term at 128^3 16.2 against
+// 13.9 ms, with as many VALU instructions as in FP64 and 156 to 179 registers (two waves per
+// SIMD); which of the two it is has not been told apart. So FP32 takes the column passes below
+// kColumnsF32, and on equal x and y lengths, the only ones with an FP32 plane kernel. The mixed modes, whose results are
 // complex128, keep the slab passes: the columns transform the axes in another order, which moves
 // FP32 roundings (2e-9 of H psi) that those results would show.
 bool local_uses_columns(const Plan &P, int fft_prec, int io_prec) {
