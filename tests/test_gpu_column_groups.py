@@ -49,10 +49,11 @@ def err(y, ref):
 
 
 @pytest.mark.parametrize("n1,n2,prec,kernels", [(32, 32, 0, COLUMNS), (32, 32, 1, COLUMNS), (48, 54, 0, COLUMNS),
-                                                (48, 54, 1, SLABS), (80, 80, 1, COLUMNS), (90, 90, 1, SLABS)])
+                                                (48, 54, 1, SLABS), (72, 120, 0, COLUMNS), (80, 80, 1, COLUMNS),
+                                                (90, 90, 1, SLABS)])
 def test_part_full_groups(n1, n2, prec, kernels):
     from paper_2501_08697_amd import binding as b
-    p = cell(n1, n2, 13, K3 if n1 < 80 else K3[:2])
+    p = cell(n1, n2, 13, K3 if n1 < 72 else K3[:2])   # 72 x 120: a plane alone on its CU
     print(f"[column groups] fft={p.fft} npw={list(p.npw)} prec={prec}", flush=True)
     dp, x = b.DeviceProblem(p), torch.from_numpy(p.psi).cuda()
     x = x.to(torch.complex64) if prec else x
